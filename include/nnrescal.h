@@ -276,7 +276,8 @@ NNRESCAL_API nnrescal_status nnrescal_select_k(const nnrescal_tensor *X, const n
  * the k x k matrices, the expanded row indices of a sparse tensor) lies in ONE static device array of
  * NNRESCAL_STATIC_SCRATCH_BYTES that the library holds on every GPU it is loaded on until the process ends.  A
  * problem takes about 4 q kp ((2 m + 2) n + 512) + 8 q m kp^2 bytes of it, kp = k rounded up to a multiple of 16,
- * plus 4 bytes per stored non-zero and format of a sparse tensor; one that takes more is rejected with
+ * plus 4 bytes per stored non-zero and format of a sparse tensor (the array is half as large again: the copy of A in
+ * operand order takes 8 bytes per element and is counted with 4); one that takes more is rejected with
  * NNRESCAL_EINVAL before any device work, and the message names both figures.  All calls on one GPU share that array: calls that overlap in time on one
  * GPU (different streams or threads) race; calls on one stream are fine.  Nothing from an earlier call is reused
  * (what must start at zero is cleared by kernels, no memset).  status_or_null (DEVICE int32, may be NULL) is set
@@ -309,7 +310,7 @@ NNRESCAL_API const char *nnrescal_last_error(const nnrescal_handle *h_or_null);
  * 2 matrix_mul_sparse (with a CSC copy one pair per iteration: the launch that clears shared rows and the launch of
  * both products of all slices; without one, a pair for X_t A of all slices and one per slice for the scatter form of
  * X_t^T A), 3 element-wise and k x k update kernels,
- * 4 the dense pass for the tail group of fewer than 8 members (one pair = one launch), 5 the A rule (the
+ * 4 the dense pass for the tail group of fewer than 8 members (one pair), 5 the A rule (the
  * n x k x k products of Eq. 2's second rule and the update itself; one pair per iteration, including the A^T A
  * pass that follows it for ranks above 32). */
 #define NNRESCAL_PROF_CLASSES 6

@@ -171,7 +171,7 @@ hipError_t dense_pass(nnrescal_handle* h, int only_slice, bool pq_cleared) {
   so.Ppart = h->det_ppart;                         // reproducible mode: panel sums stored, added up in order below
   so.timeout_flag = h->dev_error;
   so.spin_limit = h->p.handover_spin_limit;
-  if (pl.full_groups > 0) {
+  if (pl.full_members > 0) {
     Prof pf(h, 1);
     if ((e = launch_dense_stream(X, h->A_op, P, Q, d, 0, h->p.seed, h->p.delta, h->stream, so)) != hipSuccess)
       return e;
@@ -523,7 +523,7 @@ nnrescal_status init_impl(nnrescal_handle** out, const nnrescal_tensor* X, const
   };
   // 8 spare member slots behind the operand copy: a rounded-up tail group reads (and discards) up to 7 members
   // past q in the last tile
-  if (dense) reqs.push_back({(void**)&h->A_op, ((size_t)d.n_pad * row + 8 * (size_t)d.kp * 16) * sizeof(float)});
+  if (dense) reqs.push_back({(void**)&h->A_op, kOperandFloats * ((size_t)d.n_pad * row + 8 * (size_t)d.kp * 16) * sizeof(float)});
   if (!dense) {
     const bool csc = h->X.format == NNRESCAL_CSR_CSC;
     reqs.push_back({(void**)&h->csr_major, (size_t)h->csr_off[d.m] * sizeof(int32_t)});
@@ -564,8 +564,8 @@ nnrescal_status init_impl(nnrescal_handle** out, const nnrescal_tensor* X, const
     return fail(nullptr, NNRESCAL_EDEVICE, msg);
   };
   hipError_t e;
-  if (dense && (e = launch_fill_zero(h->A_op + (size_t)d.n_pad * row, 8 * (size_t)d.kp * 16 * sizeof(float), h->stream)) !=
-                   hipSuccess)
+  if (dense && (e = launch_fill_zero(h->A_op + kOperandFloats * (size_t)d.n_pad * row,
+                                     kOperandFloats * 8 * (size_t)d.kp * 16 * sizeof(float), h->stream)) != hipSuccess)
     return bail(e, "clearing the operand padding");
   if (p->A0)
     e = launch_import_factors(h->A, h->R, p->A0, p->R0, d, h->stream);
@@ -827,7 +827,10 @@ int32_t nnrescal_gather_form(const nnrescal_handle* h) { return h && h->segs_dev
 // Every workspace of the iteration is carved out of this array.  In host code its name is a stand-in, not a device
 // address: the address on the current device comes from hipGetSymbolAddress, once per device, and only that pointer
 // is ever handed to kernels.
-static __device__ __align__(256) unsigned char scratch[NNRESCAL_STATIC_SCRATCH_BYTES];
+// NNRESCAL_STATIC_SCRATCH_BYTES bound what a problem may take, counted with the operand copy of A at 4 bytes per element;
+// its bf16 terms take 8.  The copy is as large as A itself (up to its padding), so at most half of the count (and 16 KB).
+constexpr size_t kScratchBytes = (size_t)NNRESCAL_STATIC_SCRATCH_BYTES + NNRESCAL_STATIC_SCRATCH_BYTES / 2 + 65536;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -926,12 +929,13 @@ nnrescal_status nnrescal_mu_step_static(const nnrescal_tensor* X, const nnrescal
   size_t off = 0;
   for (const Req& r : reqs) {
     *r.p = r.bytes ? (void*)(base + off) : nullptr;
-    off += (r.bytes + 255) & ~(size_t)255;
+    off += ((r.p == (void**)&h->A_op ? kOperandFloats : 1) * r.bytes + 255) & ~(size_t)255;
   }
+  if (off > kScratchBytes) return fail(nullptr, NNRESCAL_EINVAL, "nnrescal_mu_step_static: workspace beyond the static array");
   h->dev_error = status_or_null;       // a device word of the caller's (or none)
   h->dev_error_pinned = false;
   if (status_or_null) HIPCHK(launch_fill_zero(status_or_null, sizeof(int32_t), h->stream));
-  if (dense) HIPCHK(launch_fill_zero(h->A_op + (size_t)d.n_pad * row, pad * sizeof(float), h->stream));
+  if (dense) HIPCHK(launch_fill_zero(h->A_op + kOperandFloats * (size_t)d.n_pad * row, kOperandFloats * pad * sizeof(float), h->stream));
   HIPCHK(launch_import_factors(h->A, h->R, A, R, d, h->stream));
   if (!dense) {
     for (int t = 0; t < d.m; ++t) {

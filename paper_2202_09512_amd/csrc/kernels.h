@@ -1,8 +1,8 @@
 // Host-side launchers of the HIP kernels.  Layouts (all fp32 unless noted):
 //   A_int  [n_pad][q][kp]   entity-major factor of all members; kp = k rounded up to a multiple of 16;
 //                           columns >= k and rows >= n are zero and stay zero
-//   A_op   [n_pad/16][q][kp/16][64][4]   the same numbers in MFMA operand order (dense path only), rebuilt
-//                           from A_int before every pass over X
+//   A_op   [n_pad/16][q][kp/16][2][64] x 16 bytes   the same numbers as bf16 terms in MFMA operand order (dense path
+//                           only), written by the A rule with every new A
 //   R      [q][m][k][k]
 //   G, W   [q][k][k]        A^T A and the k x k core of the A denominator
 //   S      [m][q][k][k]     A^T X_t A
@@ -102,17 +102,18 @@ hipError_t launch_a_update16(float* A_int, float* A_op, const float* P, const fl
                              float* det_part = nullptr, size_t det_part_floats = 0);
 
 // ---- dense pass over X (kernels_dense.hip)
-// A_op[tile][member][block][lane][r] = A_int[16*tile + 4*(lane/16) + r][member][16*block + lane%16]
+// A_op[tile][member][block][half][lane]: the bf16 terms (y1 | y2), (y1 | y3) of A_int[16*tile + 4*(lane/16) + r][member]
+// [16*block + lane%16], r = 0..3: kOperandFloats floats of memory per element of A
+constexpr int kOperandFloats = 2;
 // n_rows: rows that A_int really holds (default: n_pad); the rest of the copy is zero
 hipError_t launch_pack_operand(const float* A_int, float* A_op, const Dims& d, hipStream_t s, int64_t n_rows = -1);
 // For every slice t and member r: P[t][i][r][:] = sum_j X[t][i][j] Delta^r[t][i][j] A[j][r][:],
 //                                 Q[t][j][r][:] = sum_i X[t][i][j] Delta^r[t][i][j] A[i][r][:].
 // P and Q must be zero on entry (partial sums are added atomically); the launcher does not clear them.
-// The members are processed in groups that share one Philox block: `full` launches cover the groups of
-// 8 members (4 for kp = 32, 2 for kp > 32), `tail` the remaining members rounded up to a power of two.
-// part 0 = full groups, part 1 = tail group; a part with no members launches nothing.
+// The members are taken in groups, each group's elements drawn from one Philox block.  part 0 = the members of whole groups
+// of 8 (4 for kp = 32, 2 above), part 1 = the others; a part with no members launches nothing.
 struct DensePlan {
-  int full_groups, full_qb, tail_members, tail_qb;
+  int full_members, tail_members;
 };
 DensePlan dense_stream_plan(const Dims& d);
 int64_t dense_stream_panels(const Dims& d);   // 128-column panels of a slice
@@ -120,7 +121,7 @@ struct DenseStreamOpts {
   int t_first = 0;               // slice index that X (and P, Q) start at, for callers that pass a part of the tensor:
                                  // the random stream is keyed by the slice's index in the whole tensor
   const float* A_opQ = nullptr;  // right operand of the second product (X^T .), if it is to differ from the first one's
-  int64_t aop_tstride = 0;       // floats between the operand arrays of consecutive slices (0: the same for every slice)
+  int64_t aop_tstride = 0;       // floats of memory between the operand arrays of consecutive slices (0: the same for every slice)
   int64_t out_tstride = -1;      // floats between the slices of P and of Q (default n*q*kp; 0 sums the products over
                                  // the slices)
   int32_t* timeout_flag = nullptr;  // set to 1 (device or pinned host word) when a bounded wait inside the kernel ran

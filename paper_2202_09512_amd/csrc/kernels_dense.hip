@@ -3,73 +3,74 @@
 // with X^r = X (*) Delta^r generated on the fly (Alg. 4) from a counter-based random stream, so the
 // perturbed tensors are never stored and X is read once for all members of a group.
 //
-// Mapping to CDNA4.  The contraction runs on fp32 matrix cores, v_mfma_f32_16x16x4f32
-// (D[16x16] += A[16x4] B[4x16]; lane l supplies A[l%16][l/16] and B[l/16][l%16], and holds
-// D[4*(l/16)+r][l%16] in register r).  The perturbed X tile is the MFMA's left operand, built in
-// registers by the lane that loaded the element; rows of the factor are the right operand, read from a
-// copy of A that is stored in operand order (one 16-byte load per lane and product group).
+// Mapping to CDNA4.  The contraction runs on the bf16 matrix cores at fp32 precision: every operand is a sum of three
+// bf16 terms and a 16 x 16 x 16 product of fp32 numbers is three v_mfma_f32_16x16x32_bf16 (bf16split.h).  They take 50
+// cycles; the four v_mfma_f32_16x16x4_f32 of the same product take 129 and, sharing the vector ALUs, let no vector
+// instruction run beside them, while the generator's multiplications run beside bf16 MFMA for free (measured).
+// Of an instruction's result D[16x16], lane l holds D[4*(l/16)+r][l%16] in register r.  The perturbed X tile is the left
+// operand, built in registers by the lane that loaded the element; rows of the factor are the right operand, read from
+// a copy of A that is stored in operand order (two 16-byte loads per lane and product group).
 //
 // A workgroup of 8 waves owns a panel of 128 columns (8 tiles) and a chunk of rows.  In a round, every wave
 // takes one 16-row strip and walks it across the panel, tile by tile:
 //   - the strip's P accumulators and the right operands of the Q products (the strip's 16 factor rows) stay
 //     in registers for the whole strip; P is added to memory once per strip;
-//   - the tile is parked in LDS and read back transposed for the Q product, so the generator runs once per
-//     element;
+//   - the tile's terms are parked in LDS and read back transposed (ds_read_b64_tr_b16) for the Q product, so the
+//     generator and the split into terms run once per element;
 //   - the panel's Q accumulators live in LDS in accumulator order.  In step s wave w works on tile
-//     (w + s) % 8, so at any time each tile column has one owner, which loads the accumulators as the MFMA's
-//     C operand and stores the result back: no atomics and no cross-wave reduction.  A column passes from
+//     (w + s) % 8, so at any time each tile column has one owner, which adds the tile's products to the
+//     accumulators: no atomics and no cross-wave reduction.  (The bf16 instruction cuts what lies 2^-8 of its C
+//     operand's last place or deeper.  Over the thousands of instructions of a chunk that added up to 2.8e-7 of Q, always
+//     downwards; with a tile's products summed from zero and added by vector instructions Q is off by 1.5e-9 in the
+//     mean and 1.2e-7 in all at n = 16384, with fp32 MFMA it was 4.8e-7.)  A column passes from
 //     wave w + 1 to wave w; every wave counts its completed steps in LDS and waits only for that neighbour,
 //     before the Q half of its step (no barrier per step).  Q is added to memory once per workgroup.
-// On gfx950 fp32 MFMA and ordinary vector instructions use the same ALUs and do not overlap (measured), so
-// the floor of a tile is its MFMA time plus the generator's and the conversions' vector time.
 // One Philox block yields eight 16-bit draws, one per member of the group, so the generator's integer
 // work is shared by up to 8 members.
-#include "common.h"
+//
+// What bounds it: the vector instructions of a tile (generator, splitting, conversions), with two waves per SIMD at 256
+// registers each; the additions of P to memory cost another 17 % (measured by leaving them out).  Against the kernel with
+// fp32 MFMA, one launch for all slices: n = 16384, 4 slices, 8 members, rank 16: 7.02 -> 6.48 ms; n = 2160, 20 slices, 8
+// members, rank 24: 1337 -> 1113 us; n = 2048, 8 slices, 6 members, rank 64: 670 -> 512 us.
+// Measured and left out: one Philox block shared by a pair of waves through LDS (6.8 ... 7.2 ms at n = 16384: the pair
+// waits for each other), a wave that generates beside one that multiplies (7.1 ms), 16 waves per workgroup with half the
+// registers each (6.6 ... 6.9 ms).
+#include "bf16split.h"
 #include "kernels.h"
 
 namespace nnr {
-
 // Issue priority of a wave by the phase of its step (s_setprio; it only orders the waves of a SIMD, not streams):
 // lowest in the long vector-only generator phase, higher once the matrix products start, highest from the tile
-// transposition to the end of the step.  The wave that is nearer to handing its tile column on goes first; measured
-// against equal priorities: 59.4 -> 52.9 ms per launch on the 16384-entity workload.  Only the order matters
-// (generator < P products < rest); with the P products at or above the rest the gain is half, at the generator's
-// level it is gone.
+// transposition to the end of the step.  The wave that is nearer to handing its tile column on goes first; measured at
+// n = 16384 (4 slices, 8 members): equal priorities 2 % slower, the opposite order 3 %.
 constexpr int kPrioGenerator = 0, kPrioPProducts = 1, kPrioRest = 2;
 
+constexpr int kWaves = 8;
+constexpr int kPanel = 16 * kWaves;
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kWaves = 8;     // two waves per SIMD
-constexpr int kPanel = 128;   // columns per workgroup
-constexpr int kTiles = kPanel / 16;
-constexpr int kTLD = 20;      // row pitch (floats) of a 16 x 16 transposition tile in LDS: conflict-free reads
-
-// Operand-order copy of the factor: A_op[entity / 16][member][column block][lane][r] =
-//   A_int[16 * (entity / 16) + 4 * (lane / 16) + r][member][16 * block + lane % 16]
-// so that the right MFMA operand of a 16-entity tile, for the four sub-steps r of a product, is one float4 per lane.
+// Operand-order copy of the factor, A_op[entity / 16][member][column block][half][lane] (16 bytes each): the two right
+// operands of a lane (bf16split.h) for the values
+//   A_int[16 * (entity / 16) + 4 * (lane / 16) + r][member][16 * block + lane % 16], r = 0..3.
 // Rows at or beyond n_rows (the source may end there) read as zero.
-__global__ void pack_operand_kernel(const float* __restrict__ A_int, float* __restrict__ A_op, int64_t n_pad, int q,
+__global__ void pack_operand_kernel(const float* __restrict__ A_int, uintx4* __restrict__ A_op, int64_t n_pad, int q,
                                     int kp, int64_t n_rows) {
   const int nt = kp / 16;
-  const int64_t total = n_pad * q * kp / 4;   // float4 elements
+  const int64_t total = n_pad * q * kp / 4;   // lanes of all operands
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.x * blockDim.x) {
     const int lane = (int)(idx & 63);
     int64_t rest = idx >> 6;
     const int b = (int)(rest % nt);
+    const int64_t op = rest;
     rest /= nt;
     const int mem = (int)(rest % q);
     const int64_t tile = rest / q;
     const int64_t i = tile * 16 + 4 * (lane >> 4);
     const int64_t rs = (int64_t)q * kp;
     const float* src = A_int + (i * q + mem) * kp + b * 16 + (lane & 15);
-    float4 v;
-    v.x = i + 0 < n_rows ? src[0] : 0.0f;
-    v.y = i + 1 < n_rows ? src[rs] : 0.0f;
-    v.z = i + 2 < n_rows ? src[2 * rs] : 0.0f;
-    v.w = i + 3 < n_rows ? src[3 * rs] : 0.0f;
-    reinterpret_cast<float4*>(A_op)[idx] = v;
+    const float v[4] = {i + 0 < n_rows ? src[0] : 0.0f, i + 1 < n_rows ? src[rs] : 0.0f,
+                        i + 2 < n_rows ? src[2 * rs] : 0.0f, i + 3 < n_rows ? src[3 * rs] : 0.0f};
+    store_terms(A_op + op * 128 + lane, operand_terms(v));
   }
 }
 
@@ -77,28 +78,20 @@ hipError_t launch_pack_operand(const float* A_int, float* A_op, const Dims& d, h
   const int64_t total = d.n_pad * d.q * d.kp / 4;
   int64_t blocks = ceil_div(total, 256);
   if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(pack_operand_kernel, dim3((unsigned)blocks), dim3(256), 0, s, A_int, A_op, d.n_pad, d.q, d.kp,
+  hipLaunchKernelGGL(pack_operand_kernel, dim3((unsigned)blocks), dim3(256), 0, s, A_int, (uintx4*)A_op, d.n_pad, d.q, d.kp,
                      n_rows < 0 ? d.n_pad : n_rows);
   return hipGetLastError();
 }
 
-// Load the "row" orientation of one 16 x 16 tile: lane (l16, row) gets X[i0 + l16][j0 + 4*row + r], r = 0..3.
-// full: the tile lies inside the chunk and the matrix, rows are 16-byte aligned (one vector load, no mask).
-__device__ __forceinline__ float4 load_tile(const float* __restrict__ xtile, bool full, int n32, int rows_left,
-                                            int cols_left, int l16, int row) {
-  if (full) return *reinterpret_cast<const float4*>(xtile + (l16 * n32 + 4 * row));
-  // clamp the address into the valid part of the tile, then mask: no divergent branches
-  const int ic = l16 < rows_left ? l16 : rows_left - 1;
-  const bool rok = l16 < rows_left;
-  float x[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = 4 * row + r;
-    const int jc = j < cols_left ? j : cols_left - 1;
-    const float v = xtile[ic * n32 + jc];
-    x[r] = (rok && j < cols_left) ? v : 0.0f;
-  }
-  return float4{x[0], x[1], x[2], x[3]};
+// The "row" orientation of one 16 x 16 tile: lane (l16, row) holds X[i0 + l16][j0 + 4*row + r], r = 0..3.  It is ONE
+// 16-byte buffer load per lane on every path (rows need no more than the 4-byte alignment of a float; what lies beyond
+// the tensor's end reads as zero), so that the number of loads in flight is known wherever one of them is waited for.
+// take_tile puts zeros in the places of other rows and columns.
+__device__ __forceinline__ floatx4 take_tile(floatx4 x, int rows_left, int cols_left) {
+  // rows_left, cols_left: elements of the matrix from this lane's first one on
+  const bool in = rows_left > 0;
+  return floatx4{in && cols_left > 0 ? x.x : 0.0f, in && cols_left > 1 ? x.y : 0.0f, in && cols_left > 2 ? x.z : 0.0f,
+                 in && cols_left > 3 ? x.w : 0.0f};
 }
 
 // The 16-bit halves [hoff, hoff + QB) of a Philox block moved to its front, so that the members of a group index the
@@ -117,44 +110,69 @@ __device__ __forceinline__ u32x4 front_halves(u32x4 w, int hoff) {
   return w;
 }
 
+// How a member's perturbed element is split into bf16 terms (left operand x1 + d1 + d2 of both products):
+//   kPlain       delta = 0: the three terms of X itself, one split for all members;
+//   kSharedHead  delta <= kSharedHeadMaxDelta: x1 is the head of X, common to the members of a group; d1 + d2 is the
+//                member's distance from it, at most (delta + 2^-7) X, which two terms hold to 2^-18 of that;
+//   kOwnHead     larger delta: every member has a head of its own.
+enum { kPlain = 0, kSharedHead = 1, kOwnHead = 2 };
+
 // Dynamic LDS layout (floats):
-//   [0, kTiles*NG*256)          panel-wide Q accumulator in MFMA accumulator order: qlds[tile][group][lane][4]
-//   then per wave QB*16*kTLD    transposition tiles of the members of the group
+//   [0, kWaves*NG*256)          panel-wide Q accumulator in MFMA accumulator order: qlds[tile][group][lane][4]
+//   then per wave               transposition tiles of bf16 terms: 64 pieces of 8 bytes per
+//                               term, d1 and d2 of every member, then the head(s) x1
 //   then kWaves ints            completed steps per wave
-template <int NT, int QB, bool PERTURB>
+template <int NT, int QB, int MODE>
+struct StreamShape {
+  static constexpr int NG = QB * NT;                            // product groups (member, 16-column block)
+  static constexpr int NREST = MODE == kPlain ? 1 : QB;         // rests (d1, d2) per element
+  static constexpr int NHEAD = MODE == kOwnHead ? QB : 1;       // heads (x1) per element
+  static constexpr int QLDS = kWaves * NG * 256;               // floats of the Q accumulator
+  static constexpr int TBUF = NREST * 256 + NHEAD * 128;        // floats of transposition space per wave
+  static constexpr size_t bytes = (size_t)(QLDS + kWaves * TBUF + kWaves) * sizeof(float);
+};
+
+// four 16-bit values of one column of a row-major LDS tile (the 16 lanes of a group each address four of a row)
+__device__ __forceinline__ uintx2 read_transposed(const void* lds_ptr) {
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                        (__attribute__((address_space(3))) s4*)(__attribute__((address_space(3))) void*)lds_ptr));
+}
+
+template <int NT, int QB, int MODE>
 __global__ void __launch_bounds__(kWaves * 64)
-    dense_stream_kernel(const float* __restrict__ X, const float* __restrict__ A_op, float* __restrict__ P,
-                        float* __restrict__ Q, int64_t n, int q, int kp, int qfirst, int ngroups, int n_panels,
-                        int n_chunks, int64_t rows_per_chunk, uint32_t k0, uint32_t k1, float dscaled, int vec_ok,
-                        int t_first, const float* __restrict__ A_opQ, int64_t aop_tstride, int64_t out_tstride,
+    dense_stream_kernel(const float* __restrict__ X, const uintx4* __restrict__ A_op, float* __restrict__ P,
+                        float* __restrict__ Q, int64_t n, int m, int q, int k, int qfirst, int ngroups, int n_chunks,
+                        int64_t rows_per_chunk, uint32_t k0, uint32_t k1, float dscaled, int t_first,
+                        const uintx4* __restrict__ A_opQ, int64_t aop_tstride, int64_t out_tstride,
                         int32_t* __restrict__ timeout_flag, int spin_limit, float* __restrict__ Ppart,
                         int64_t ppart_stride) {
-  constexpr int NG = QB * NT;                       // product groups (member, 16-column block)
-  constexpr int QLDS = kTiles * NG * 256;           // floats of the Q accumulator
-  constexpr int TBUF = QB * 16 * kTLD;              // floats of transposition space per wave
+  typedef StreamShape<NT, QB, MODE> Shape;
+  constexpr int NG = Shape::NG, NREST = Shape::NREST, NHEAD = Shape::NHEAD;
   extern __shared__ __attribute__((aligned(16))) float lds[];
   float* qlds = lds;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, row = lane >> 4;
-  float* tbuf = lds + QLDS + wave * TBUF;
+  char* tbuf = reinterpret_cast<char*>(lds + Shape::QLDS + wave * Shape::TBUF);
   // done[w]: number of steps wave w has completed (see the hand-over of the tile columns below)
-  int* done = reinterpret_cast<int*>(lds + QLDS + kWaves * TBUF);
+  int* done = reinterpret_cast<int*>(lds + Shape::QLDS + kWaves * Shape::TBUF);
   if (lane == 0) done[wave] = 0;
 
-  // Workgroups are handed to the 8 XCDs round-robin; give each XCD a contiguous range of logical indices so
-  // that the workgroups adding to the same rows of P (same chunk, neighbouring panels) share one L2.
+  // Workgroups are handed to the 8 XCDs round-robin; give each XCD a contiguous range of logical indices.  Member group
+  // and slice run fastest: the workgroups that an XCD runs at a time then work on few panels of several slices, whose
+  // operands (the same factor rows) they share in that XCD's L2, and no two of them add to the same rows of P.
   int64_t logical;
   {
     const int64_t total = gridDim.x, L = blockIdx.x;
     const int64_t base = total >> 3, rem = total & 7, xcd = L & 7, slot = L >> 3;
     logical = xcd * base + (xcd < rem ? xcd : rem) + slot;
   }
-  const int panel = (int)(logical % n_panels);
-  const int chunk = (int)((logical / n_panels) % n_chunks);
-  const int z = (int)(logical / ((int64_t)n_panels * n_chunks));
-  const int t = z / ngroups, grp = z % ngroups;
+  const int grp = (int)(logical % ngroups);
+  const int t = (int)((logical / ngroups) % m);
+  const int64_t z = logical / ((int64_t)ngroups * m);
+  const int chunk = (int)(z % n_chunks), panel = (int)(z / n_chunks);
   // Members [q0, q0 + QB) share one Philox block (QB divides 8 and q0 is a multiple of QB).  Slots at or
   // beyond q (a rounded-up tail group) are computed on whatever the spare operand slots hold and never written.
   const int q0 = qfirst + grp * QB;
@@ -165,7 +183,6 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int64_t i_begin = (int64_t)chunk * rows_per_chunk;
   int64_t i_end = i_begin + rows_per_chunk;
   if (i_end > n) i_end = n;
-  const float* Xt = X + (int64_t)t * n * n;
   // Reproducible mode (Ppart given): the panel's sums for X_t A are stored in the panel's own copy, and, the chunk
   // being the whole slice then, X_t^T A is stored by its only writer; nothing is added atomically.
   const bool ordered = Ppart != nullptr;
@@ -173,19 +190,20 @@ __global__ void __launch_bounds__(kWaves * 64)
   float* Qt = Q + (int64_t)t * out_tstride;
   const int n32 = (int)n;
   int tiles = (int)((n - jp0 + 15) >> 4);           // tiles of the panel that hold columns of the matrix
-  if (tiles > kTiles) tiles = kTiles;
+  if (tiles > kWaves) tiles = kWaves;
+  const int cols = (int)(n - jp0 < kPanel ? n - jp0 : kPanel);   // columns of the panel
 
-  for (int e = tid; e < QLDS; e += kWaves * 64) qlds[e] = 0.0f;
+  for (int e = tid; e < Shape::QLDS; e += kWaves * 64) qlds[e] = 0.0f;
   __syncthreads();
 
-  // Operand address of (tile of 16 entities, product group g), in float4 units: a wave-uniform part
+  // Operand address of (tile of 16 entities, product group g), in units of 16 bytes: a wave-uniform part
   // (tile, first member, g) plus the lane.
   // The two products may take their right operands from different arrays, and from a different one per slice
-  // (aop_tstride floats apart): the iteration itself passes the same A for both and every slice.
-  const int64_t tile_f4 = (int64_t)q * NT * 64;     // float4 per 16-entity tile
-  const float4* Ag = reinterpret_cast<const float4*>(A_opQ + (int64_t)t * aop_tstride) + (int64_t)q0 * NT * 64;
-  const float4* Ap = reinterpret_cast<const float4*>(A_op + (int64_t)t * aop_tstride) + (int64_t)q0 * NT * 64 +
-                     (jp0 >> 4) * tile_f4;          // operands of the panel's column tiles, first group of this member group
+  // (aop_tstride units apart): the iteration itself passes the same A for both and every slice.
+  const int64_t tile_u4 = (int64_t)q * NT * 128;    // units per 16-entity tile
+  const uintx4* Ag = A_opQ + (int64_t)t * aop_tstride + (int64_t)q0 * NT * 128;
+  const uintx4* Ap = A_op + (int64_t)t * aop_tstride + (int64_t)q0 * NT * 128 +
+                     (jp0 >> 4) * tile_u4;          // operands of the panel's column tiles, first group of this member group
 
   // A round = 8 strips of 16 rows, one per wave; in step s of a round wave w works on tile (w + s) % 8 of
   // its strip, so at any step every tile column of the Q accumulator belongs to one wave.  A column passes from
@@ -193,7 +211,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   // only for the one wave it takes its column from.
   const int nstrips = (int)((i_end - i_begin + 15) >> 4);
   const int nrounds = (nstrips + kWaves - 1) / kWaves;
-  auto tile_of = [&](int s) { return (wave + s) & (kTiles - 1); };
+  auto tile_of = [&](int s) { return (wave + s) & (kWaves - 1); };
   // first row of this wave's strip in round rnd (a wave without a strip, or past the last round, reads the
   // chunk's first strip: valid memory, never used)
   // The workgroups of one chunk (one per panel) add to the same rows of P; each starts at a different round so
@@ -208,33 +226,32 @@ __global__ void __launch_bounds__(kWaves * 64)
     const int strip = rnd < nrounds ? strip_of(rnd) : nstrips;
     return i_begin + 16 * (int64_t)(strip < nstrips ? strip : 0);
   };
-  // X tile of global step g = 8 * round + step; the loads run two steps ahead, across strip boundaries
-  auto x_fetch = [&](int g) -> float4 {
-    const int64_t i0 = strip_row(g >> 3);
-    const int rows_left = (int)(i_end - i0 < 16 ? i_end - i0 : 16);
-    const int jt = tile_of(g & 7);
-    const int jtc = jt < tiles ? jt : 0;            // a tile beyond the matrix: load something valid, never used
-    const int64_t j0 = jp0 + 16 * jtc;
-    const int cols_left = (int)(n - j0 < 16 ? n - j0 : 16);
-    return load_tile(Xt + i0 * n + j0, vec_ok && rows_left == 16 && cols_left == 16, n32, rows_left, cols_left, l16,
-                     row);
+  // X tile of a strip (first row i0) and a tile column; the loads run two steps ahead, across strip boundaries.  A
+  // tile beyond the matrix, or rows beyond the chunk: whatever is there is loaded and never used.
+  const int64_t total = (int64_t)m * n * n;
+  const uint32_t x_lane = (uint32_t)(l16 * n32 + 4 * row) * 4u;
+  auto x_fetch = [&](int64_t i0, int jt) -> floatx4 {
+    const int64_t first = (t * n + i0) * n + jp0;   // wave-uniform
+    const int64_t bytes = 4 * (total - first);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(X + first), 0, (int)(uint32_t)(bytes < 0xFFFFFFFFLL ? bytes : 0xFFFFFFFFLL), 0x00020000);
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_lane, 64 * jt, 0));
   };
-  float4 bP[NG], bq[NG];
+  uintx8 bP[NG], bq[NG];
   auto bp_fetch = [&](int jt) {
+    const uintx4* a = Ap + jt * (int)tile_u4;       // rows < n_pad: always valid
 #pragma unroll
-    for (int g = 0; g < NG; ++g) bP[g] = (Ap + jt * tile_f4 + g * 64)[lane];   // rows < n_pad: always valid
+    for (int g = 0; g < NG; ++g) bP[g] = load_terms(a + g * 128 + lane);
   };
   // right operands of the Q products: the strip's 16 rows of A
   auto bq_fetch = [&](int rnd) {
     const int64_t i0 = strip_row(rnd);
 #pragma unroll
-    for (int g = 0; g < NG; ++g) bq[g] = (Ag + (i0 >> 4) * tile_f4 + g * 64)[lane];
+    for (int g = 0; g < NG; ++g) bq[g] = load_terms(Ag + (i0 >> 4) * tile_u4 + g * 128 + lane);
   };
-  float4 xn1 = x_fetch(0);
-  float4 xn2 = x_fetch(1);
+  floatx4 xeven = x_fetch(strip_row(0), tile_of(0)), xodd = x_fetch(strip_row(0), tile_of(1));
   bp_fetch(tile_of(0));
   bq_fetch(0);
-  const int nsteps = nrounds * kTiles;
   // Hand-over of the tile columns: wave w may touch the column of its step g once wave w + 1 has completed g steps
   // (it had that column in step g - 1).  EVERY wave waits like this in every step before its own count moves, so
   // that a count of g + 1 implies counts of at least g, g - 1, ... down the chain.  (Every wave makes the same
@@ -261,27 +278,41 @@ __global__ void __launch_bounds__(kWaves * 64)
       __hip_atomic_store(timeout_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return arrived;
   };
+  // Transposition tiles: the lane's piece (row l16, columns 4*row ..) sits at position 4*l16 + (row ^ l16/4), so that
+  // neighbouring lanes' stores fall on different banks; read back, lane L of a group of 16 addresses row
+  // 4*group + L/4 and columns 4*(L%4) .., and gets rows 4*group .. of column L.
+  const int put = 4 * l16 + (row ^ (l16 >> 2));
+  const int get = 4 * (4 * row + (l16 >> 2)) + ((l16 & 3) ^ row);
+  char* const rest_put = tbuf + 8 * put;
+  char* const rest_get = tbuf + 8 * get;
+  char* const head_put = tbuf + NREST * 1024 + 8 * put;
+  char* const head_get = tbuf + NREST * 1024 + 8 * get;
+  const float pa = 2.0f * dscaled, pc = __fmaf_rn(-65535.0f, dscaled, 1.0f);   // as in perturbed()
 
   for (int rnd = 0; rnd < nrounds; ++rnd) {
     const int strip = strip_of(rnd);
     const bool have_strip = strip < nstrips;        // wave-uniform
-    const int64_t i0 = strip_row(rnd);
+    const int64_t i0 = strip_row(rnd), i0_next = strip_row(rnd + 1);
+    const int rows_left = (int)(i_end - i0 < 16 ? i_end - i0 : 16);
     floatx4 pacc[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) pacc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    for (int s = 0; s < kTiles; ++s) {
+    // one step; x: its tile of X, in place of which the tile of step s + 2 is requested
+    auto step = [&](const int s, floatx4& x) {
       const int jt = tile_of(s);
       const bool work = have_strip && jt < tiles;   // wave-uniform
-      const float4 xc = xn1;
-      xn1 = xn2;
-      if (rnd * kTiles + s + 2 < nsteps) xn2 = x_fetch(rnd * kTiles + s + 2);
+      floatx4 xc = x;
+      x = x_fetch(s + 2 < kWaves ? i0 : i0_next, tile_of(s + 2));
       if (work) {
+        if (rows_left < 16 || 16 * jt + 16 > cols) {          // wave-uniform
+          xc = take_tile(xc, rows_left - l16, cols - (16 * jt + 4 * row));
+        }
         const float xcur[4] = {xc.x, xc.y, xc.z, xc.w};
         // ---- the generator: one Philox block per element serves all QB members
         __builtin_amdgcn_s_setprio(kPrioGenerator);
         u32x4 w[4];
-        if (PERTURB) {
+        if (MODE != kPlain) {
           const uint64_t e0 = (uint64_t)(i0 + l16) * (uint64_t)n + (uint64_t)(jp0 + 16 * jt + 4 * row);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -290,99 +321,156 @@ __global__ void __launch_bounds__(kWaves * 64)
                 philox4x32_10((uint32_t)e, (uint32_t)(e >> 32), (uint32_t)(t + t_first), sub, k0, k1), hoff);
           }
         }
-        // ---- per member: perturbed tile in "row" orientation -> P products; park it in LDS for the transpose
+        // ---- per member: the terms of the perturbed tile in "row" orientation -> P products; park them in LDS for
+        //      the transpose
         __builtin_amdgcn_s_setprio(kPrioPProducts);
+        float xa[4], rc[4];                         // the rest of a member's element over the head: xa * half + rc
+        uintx2 x1 = {pack_cut(xcur[0], xcur[1]), pack_cut(xcur[2], xcur[3])};
+        uintx2 d1, d2;
 #pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-          float xq[4];
+        for (int r = 0; r < 4; ++r) {
+          xa[r] = __fmul_rn(xcur[r], pa);
+          rc[r] = (MODE == kPlain ? xcur[r] : __fmul_rn(xcur[r], pc)) - (MODE == kOwnHead ? 0.0f : cut_to_bf16(xcur[r]));
+        }
+        if (MODE != kOwnHead) *reinterpret_cast<uintx2*>(head_put) = x1;
+        if (MODE == kPlain) {
+          split2(rc, d1, d2);
+          *reinterpret_cast<uintx2*>(rest_put) = d1;
+          *reinterpret_cast<uintx2*>(rest_put + 512) = d2;
+        }
+        constexpr int PB = QB > 1 ? 2 : 1;          // members whose products are interleaved: a product's three
+#pragma unroll                                      // instructions wait for each other's sums
+        for (int q2 = 0; q2 < QB; q2 += PB) {
+          uintx2 e1[PB], e2[PB], h1[PB];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) xq[r] = PERTURB ? perturbed(xcur[r], w[r], qq, dscaled) : xcur[r];
-          *reinterpret_cast<float4*>(tbuf + (qq * 16 + l16) * kTLD + 4 * row) = float4{xq[0], xq[1], xq[2], xq[3]};
+          for (int u = 0; u < PB; ++u) {
+            const int qq = q2 + u;
+            if (MODE != kPlain) {
+              float d[4];
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int g = qq * NT + nt;
-            pacc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[0], bP[g].x, pacc[g], 0, 0, 0);
-            pacc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[1], bP[g].y, pacc[g], 0, 0, 0);
-            pacc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[2], bP[g].z, pacc[g], 0, 0, 0);
-            pacc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[3], bP[g].w, pacc[g], 0, 0, 0);
+              for (int r = 0; r < 4; ++r) {
+                const uint32_t word = (qq >> 1) == 0 ? w[r].x : (qq >> 1) == 1 ? w[r].y : (qq >> 1) == 2 ? w[r].z : w[r].w;
+                d[r] = __fmaf_rn(xa[r], (qq & 1) ? (float)(word >> 16) : (float)(word & 0xFFFFu), rc[r]);
+              }
+              if (MODE == kOwnHead) {               // d is the perturbed value itself
+                x1 = uintx2{pack_cut(d[0], d[1]), pack_cut(d[2], d[3])};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) d[r] -= cut_to_bf16(d[r]);
+                *reinterpret_cast<uintx2*>(head_put + 512 * qq) = x1;
+              }
+              split2(d, d1, d2);
+              *reinterpret_cast<uintx2*>(rest_put + 1024 * qq) = d1;
+              *reinterpret_cast<uintx2*>(rest_put + 1024 * qq + 512) = d2;
+            }
+            h1[u] = x1;
+            e1[u] = d1;
+            e2[u] = d2;
           }
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+              for (int u = 0; u < PB; ++u) {
+                const int g = (q2 + u) * NT + nt;
+                pacc[g] = mfma_terms(i, h1[u], e1[u], e2[u], bP[g], pacc[g]);
+              }
         }
       }
       __builtin_amdgcn_s_setprio(kPrioRest);
       // the operand registers are free again: fetch the next tile's
-      bp_fetch(tile_of((s + 1) & (kTiles - 1)));
+      bp_fetch(tile_of((s + 1) & (kWaves - 1)));
       if (work) {
-        // ---- "column" orientation read back from LDS: lane (l16, row) gets X^q[i0 + 4*row + r][j0 + l16];
-        //      the tile's Q accumulators are this wave's alone until the next barrier
+        // ---- "column" orientation read back from LDS: lane (l16, row) gets the terms of rows i0 + 4*row + r of column
+        //      j0 + l16; the tile's Q accumulators are this wave's alone until the next barrier
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         // Tile column jt was wave (wave + 1) % 8's in the previous step: wait until that wave has completed it.
-        const bool mine = wait_for_neighbour(rnd * kTiles + s);   // wave-uniform
+        const bool mine = wait_for_neighbour(rnd * kWaves + s);   // wave-uniform
         float4* qt = reinterpret_cast<float4*>(qlds) + (jt * NG) * 64 + lane;
-        // all LDS reads first (one wait), then the products back to back, then the stores
-        float xt[QB][4];
-        floatx4 qa[NG];
+        // QH members at a time: all LDS reads first (one wait), then the products back to back, then the stores (with all
+        // 8 groups at a time the registers run out; halves spill 8 and are 2 % slower than quarters at n = 16384)
+        constexpr int QH = NG < 8 || QB == 1 ? QB : (QB > 2 ? QB / 4 : 1);
+        uintx2 x1t[NHEAD];
+        if (MODE != kOwnHead) x1t[0] = read_transposed(head_get);
 #pragma unroll
-        for (int qq = 0; qq < QB; ++qq)
+        for (int q1 = 0; q1 < QB; q1 += QH) {
+          uintx2 d1t[QH], d2t[QH];
+          floatx4 qa[QH * NT];
+          float4 c[QH * NT];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) xt[qq][r] = tbuf[(qq * 16 + 4 * row + r) * kTLD + l16];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          const float4 c = qt[g * 64];
-          qa[g] = floatx4{c.x, c.y, c.z, c.w};
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int g = qq * NT + nt;
-            qa[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt[qq][0], bq[g].x, qa[g], 0, 0, 0);
-            qa[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt[qq][1], bq[g].y, qa[g], 0, 0, 0);
-            qa[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt[qq][2], bq[g].z, qa[g], 0, 0, 0);
-            qa[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt[qq][3], bq[g].w, qa[g], 0, 0, 0);
+          for (int h = 0; h < QH; ++h) {
+            if (MODE == kOwnHead) x1t[q1 + h] = read_transposed(head_get + 512 * (q1 + h));
+            if (NREST > 1 || h == 0) {
+              const int at = NREST > 1 ? 1024 * (q1 + h) : 0;
+              d1t[h] = read_transposed(rest_get + at);
+              d2t[h] = read_transposed(rest_get + at + 512);
+            }
           }
-        __builtin_amdgcn_sched_barrier(0);
-        if (mine) {
 #pragma unroll
-          for (int g = 0; g < NG; ++g) qt[g * 64] = float4{qa[g][0], qa[g][1], qa[g][2], qa[g][3]};
+          for (int g = 0; g < QH * NT; ++g) {
+            c[g] = qt[(q1 * NT + g) * 64];
+            qa[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int g = 0; g < QH * NT; ++g) {
+              const int h = g / NT;
+              qa[g] = mfma_terms(i, x1t[NHEAD == 1 ? 0 : q1 + h], d1t[NREST == 1 ? 0 : h], d2t[NREST == 1 ? 0 : h],
+                                 bq[q1 * NT + g], qa[g]);
+            }
+          __builtin_amdgcn_sched_barrier(0);
+          if (mine) {
+#pragma unroll
+            for (int g = 0; g < QH * NT; ++g)
+              qt[(q1 * NT + g) * 64] = float4{c[g].x + qa[g][0], c[g].y + qa[g][1], c[g].z + qa[g][2], c[g].w + qa[g][3]};
+          }
         }
       } else {
         // A wave with nothing to do in this step (no strip in the chunk's last round, or a tile beyond the matrix)
         // still is a link of the chain: its count may move only after its neighbour's, or the wave behind it
         // could take the column over while the wave in front is still working on it.
-        (void)wait_for_neighbour(rnd * kTiles + s);
+        (void)wait_for_neighbour(rnd * kWaves + s);
       }
       // the strip's last Q products are done: fetch the next strip's operands behind them
-      if (s == kTiles - 1 && rnd + 1 < nrounds) bq_fetch(rnd + 1);
+      if (s == kWaves - 1 && rnd + 1 < nrounds) bq_fetch(rnd + 1);
       // hand the tile column on: the accumulators are in LDS before the count moves
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0)
-        __hip_atomic_store(&done[wave], rnd * kTiles + s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&done[wave], rnd * kWaves + s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll 1
+    for (int s = 0; s < kWaves; s += 2) {           // (two steps per trip: the two tiles in flight keep their registers)
+      step(s, xeven);
+      step(s + 1, xodd);
     }
-    // ---- the strip's P (16 rows, summed over the panel's columns): add to memory
+    // ---- the strip's P (16 rows, summed over the panel's columns): add to memory.  The groups of a row are neighbours
+    //      (kp = 16 NT): one 32-bit offset per register r, the group in the instruction's immediate offset.
     if (have_strip) {
+      char* prow = reinterpret_cast<char*>(Pt + (i0 * q + q0) * (16 * NT));   // wave-uniform
+      int ln = lane;
+      asm volatile("" : "+v"(ln));                  // (keeps the offsets from being computed ahead of the loop and held there)
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int qq = g / NT, nt = g % NT;
-        if (qq < qb) {
+      for (int r = 0; r < 4; ++r) {
+        const int rr = 4 * (ln >> 4) + r;
+        if (rr >= rows_left) continue;
+        const uint32_t off = (uint32_t)(rr * q * (16 * NT) + (ln & 15)) * 4u;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int64_t i = i0 + 4 * row + r;
-            const float v = pacc[g][r];
-            if (ordered) {
-              if (i < i_end) Pt[(i * q + q0 + qq) * kp + nt * 16 + l16] = v;
-            } else if (i < i_end && v != 0.0f) {
-              unsafeAtomicAdd(&Pt[(i * q + q0 + qq) * kp + nt * 16 + l16], v);
-            }
-          }
+        for (int g = 0; g < NG; ++g) {
+          float* at = reinterpret_cast<float*>(prow + off + 64 * g);
+          if (g / NT >= qb) break;
+          if (ordered) *at = pacc[g][r];
+          else if ((g % NT) * 16 + (ln & 15) < k) unsafeAtomicAdd(at, pacc[g][r]);
         }
       }
     }
   }
   __syncthreads();
   // ---- the panel's Q (summed over the chunk's rows): add to memory (every wave has made its last step)
+  constexpr int kp = 16 * NT;
   for (int e = tid; e < tiles * NG * 256; e += kWaves * 64) {
     const float v = qlds[e];
     const int r = e & 3, ln = (e >> 2) & 63, g = (e >> 8) % NG, jt = (e >> 8) / NG;
@@ -396,19 +484,13 @@ __global__ void __launch_bounds__(kWaves * 64)
   }
 }
 
-template <int NT, int QB>
-constexpr size_t stream_lds_bytes() {
-  return (size_t)(kTiles * QB * NT * 256 + kWaves * QB * 16 * kTLD + kWaves) * sizeof(float);
-}
-
 const char* dense_stream_kernel_name() { return "dense_stream_kernel"; }
 
-template <int NT, int QB>
+template <int NT, int QB, int MODE>
 static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qfirst,
                                   int ngroups, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   const int t_first = o.t_first;
   const float* A_opQ = o.A_opQ ? o.A_opQ : A_op;
-  const int64_t aop_tstride = o.aop_tstride;
   const int64_t out_tstride = o.out_tstride < 0 ? d.n * d.q * (int64_t)d.kp : o.out_tstride;
   int32_t* timeout_flag = o.timeout_flag;
   const int spin_limit = o.spin_limit > 0 ? o.spin_limit : (o.spin_limit < 0 ? 0 : (1 << 20));
@@ -416,16 +498,12 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
   const int64_t ppart_stride = (int64_t)d.m * d.n * d.q * d.kp;   // one copy of P per panel
   if (Ppart && out_tstride != d.n * d.q * (int64_t)d.kp) return hipErrorInvalidValue;   // (not with summed slices)
   static_assert(QB * NT <= 8, "at most 8 product groups per tile");
-  static_assert(kTiles == kWaves && (kTiles & (kTiles - 1)) == 0, "one tile column per wave and step");
-  constexpr size_t lds = stream_lds_bytes<NT, QB>();
+  constexpr size_t lds = StreamShape<NT, QB, MODE>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, true>,
+    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, MODE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, false>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
@@ -435,10 +513,10 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
   // workgroup (clearing and adding out its share of Q, filling its pipeline: about 7 steps, i.e. the time of
   // ~112 rows, measured).  Pick the count with the least estimated time.
   const int64_t base = n_panels * d.m * ngroups;
-  const int64_t max_chunks = ceil_div(d.n, 16 * kWaves);
+  const int64_t max_chunks = ceil_div(d.n, kPanel);
   int64_t n_chunks = 1, best = -1;
   for (int64_t c = 1; c <= max_chunks && c <= 256; ++c) {
-    const int64_t rows = round_up(ceil_div(d.n, c), 16 * kWaves);
+    const int64_t rows = round_up(ceil_div(d.n, c), kPanel);
     const int64_t waves_of_wgs = ceil_div(base * ceil_div(d.n, rows), 256);
     // (a single wave of workgroups measured 20 % slower than two of half the length: nothing overlaps its ends)
     const int64_t cost = waves_of_wgs * (rows + 112) * (waves_of_wgs == 1 ? 5 : 4);
@@ -448,22 +526,22 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
     }
   }
   if (Ppart) n_chunks = 1;                          // one workgroup per panel and slice: the only writer of its X_t^T A
-  const int64_t rows_per_chunk = round_up(ceil_div(d.n, n_chunks), 16 * kWaves);
+  const int64_t rows_per_chunk = round_up(ceil_div(d.n, n_chunks), kPanel);
   n_chunks = ceil_div(d.n, rows_per_chunk);
   const int64_t total = n_panels * n_chunks * d.m * ngroups;
   if (total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  const int vec_ok = (d.n % 4 == 0) && (((uintptr_t)X & 15) == 0);
-  if (delta != 0.0f)
-    hipLaunchKernelGGL((dense_stream_kernel<NT, QB, true>), dim3((unsigned)total), dim3(kWaves * 64), lds, s, X, A_op, P,
-                       Q, d.n, d.q, d.kp, qfirst, ngroups, (int)n_panels, (int)n_chunks, rows_per_chunk, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), delta * 0x1p-16f, vec_ok, t_first, A_opQ, aop_tstride, out_tstride,
-                       timeout_flag, spin_limit, Ppart, ppart_stride);
-  else
-    hipLaunchKernelGGL((dense_stream_kernel<NT, QB, false>), dim3((unsigned)total), dim3(kWaves * 64), lds, s, X, A_op,
-                       P, Q, d.n, d.q, d.kp, qfirst, ngroups, (int)n_panels, (int)n_chunks, rows_per_chunk,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), 0.0f, vec_ok, t_first, A_opQ, aop_tstride, out_tstride,
-                       timeout_flag, spin_limit, Ppart, ppart_stride);
+  hipLaunchKernelGGL((dense_stream_kernel<NT, QB, MODE>), dim3((unsigned)total), dim3(kWaves * 64), lds, s, X,
+                     (const uintx4*)A_op, P, Q, d.n, d.m, d.q, d.k, qfirst, ngroups, (int)n_chunks, rows_per_chunk,
+                     (uint32_t)seed, (uint32_t)(seed >> 32), delta * 0x1p-16f, t_first, (const uintx4*)A_opQ,
+                     o.aop_tstride / 4, out_tstride, timeout_flag, spin_limit, Ppart, ppart_stride);
   return hipGetLastError();
+}
+
+// Up to this delta the members' elements share the head of X's (see kSharedHead): the products that are left out
+// (terms of order delta 2^-18 of the result) are then below 2^-22 of it, random in sign, under the rounding of fp32 sums.
+constexpr float kSharedHeadMaxDelta = 0.0625f;
+static int split_mode(float delta) {
+  return delta == 0.0f ? kPlain : (delta <= kSharedHeadMaxDelta ? kSharedHead : kOwnHead);
 }
 
 // Members per group so that (members) x (16-column blocks) <= 8 product groups: 8 members for k <= 16,
@@ -473,51 +551,55 @@ static int group_members(int kp) { return kp <= 16 ? 8 : (kp <= 32 ? 4 : 2); }
 int64_t dense_stream_panels(const Dims& d) { return ceil_div(d.n, kPanel); }
 
 DensePlan dense_stream_plan(const Dims& d) {
-  const int qbig = group_members(d.kp);
-  DensePlan pl;
-  pl.full_groups = d.q / qbig;
-  pl.full_qb = qbig;
-  pl.tail_members = d.q - pl.full_groups * qbig;
-  pl.tail_qb = pl.tail_members == 0 ? 0 : 1;
-  while (pl.tail_qb < pl.tail_members) pl.tail_qb *= 2;
-  return pl;
+  const int big = group_members(d.kp);
+  return DensePlan{d.q / big * big, d.q % big};
 }
 
 template <int NT, int QB>
-static hipError_t launch_tail(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf,
-                              uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  if constexpr (QB * NT <= 8)
-    return launch_stream_t<NT, QB>(X, A_op, P, Q, d, qf, 1, seed, delta, s, o);
-  else
-    return hipErrorInvalidValue;
+static hipError_t launch_stream_qb(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int ngroups,
+                                   uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  if constexpr (QB * NT <= 8) {
+    switch (split_mode(delta)) {
+      case kPlain: return launch_stream_t<NT, QB, kPlain>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+      case kSharedHead: return launch_stream_t<NT, QB, kSharedHead>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+      default:
+        if constexpr (QB <= 4) return launch_stream_t<NT, QB, kOwnHead>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
+// Members [qf, qf + count): whole groups in one launch, a rest in one of a group rounded up to a power of two.
 template <int NT>
-static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int part,
+static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int count,
                                    uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  constexpr int QBIG = NT == 1 ? 8 : (NT == 2 ? 4 : 2);
-  const DensePlan pl = dense_stream_plan(d);
-  if (part == 0) {
-    if (pl.full_groups == 0) return hipSuccess;
-    return launch_stream_t<NT, QBIG>(X, A_op, P, Q, d, 0, pl.full_groups, seed, delta, s, o);
+  int qb = group_members(d.kp);
+  if (split_mode(delta) == kOwnHead && qb > 4) qb = 4;   // (8 members' transposition tiles with their heads exceed the LDS)
+  hipError_t e = hipSuccess;
+  while (count > 0 && e == hipSuccess) {
+    while (qb / 2 >= count) qb /= 2;
+    const int groups = count < qb ? 1 : count / qb;
+    switch (qb) {
+      case 1: e = launch_stream_qb<NT, 1>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      case 2: e = launch_stream_qb<NT, 2>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      case 4: e = launch_stream_qb<NT, 4>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      default: e = launch_stream_qb<NT, 8>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+    }
+    qf += groups * qb;
+    count -= groups * qb;
   }
-  const int qf = pl.full_groups * QBIG;
-  switch (pl.tail_qb) {
-    case 0: return hipSuccess;
-    case 1: return launch_tail<NT, 1>(X, A_op, P, Q, d, qf, seed, delta, s, o);
-    case 2: return launch_tail<NT, 2>(X, A_op, P, Q, d, qf, seed, delta, s, o);
-    case 4: return launch_tail<NT, 4>(X, A_op, P, Q, d, qf, seed, delta, s, o);
-    default: return launch_tail<NT, 8>(X, A_op, P, Q, d, qf, seed, delta, s, o);
-  }
+  return e;
 }
 
 hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int part,
                                uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  const DensePlan pl = dense_stream_plan(d);
+  const int qf = part == 0 ? 0 : pl.full_members, count = part == 0 ? pl.full_members : pl.tail_members;
   switch (d.kp / 16) {
-    case 1: return launch_stream_nt<1>(X, A_op, P, Q, d, part, seed, delta, s, o);
-    case 2: return launch_stream_nt<2>(X, A_op, P, Q, d, part, seed, delta, s, o);
-    case 3: return launch_stream_nt<3>(X, A_op, P, Q, d, part, seed, delta, s, o);
-    case 4: return launch_stream_nt<4>(X, A_op, P, Q, d, part, seed, delta, s, o);
+    case 1: return launch_stream_nt<1>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
+    case 2: return launch_stream_nt<2>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
+    case 3: return launch_stream_nt<3>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
+    case 4: return launch_stream_nt<4>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
     default: return hipErrorInvalidValue;
   }
 }

@@ -11,12 +11,10 @@
 //
 // v_mfma_f32_16x16x4f32: D[16x16] += A[16x4] B[4x16]; lane l supplies A[l%16][l/16] and B[l/16][l%16] and
 // holds D[4*(l/16)+r][l%16] in register r.
-#include "common.h"
+#include "bf16split.h"
 #include "kernels.h"
 
 namespace nnr {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------ Gram over rows
 // out[(b1*q + mem)][a][c] = sum_i Y[i][mem][a] * Z_b1[i][mem][c],  a, c < k.   One wave per (batch of TB values
@@ -459,8 +457,7 @@ __global__ void __launch_bounds__(kAupdWaves * 64, WPS)
           if (ok) *ap = v;
         }
         if (A_op)
-          reinterpret_cast<float4*>(A_op)[((tile * q + mem) * NT + cb) * 64 + lane] =
-              float4{anew[cb][0], anew[cb][1], anew[cb][2], anew[cb][3]};
+          store_terms(reinterpret_cast<uintx4*>(A_op) + ((tile * q + mem) * NT + cb) * 128 + lane, operand_terms(anew[cb]));
       }
       // next iteration's A^T A: the new tile is at once the left and the right operand (rows on the K dimension)
       if constexpr (FUSE_G) {
@@ -696,8 +693,7 @@ __global__ void __launch_bounds__(WAVES * 64)
           if (ok) *ap = v;
         }
         if (A_op)
-          reinterpret_cast<float4*>(A_op)[((tile * q + mem) * NT + cb) * 64 + lane] =
-              float4{anew[cb][0], anew[cb][1], anew[cb][2], anew[cb][3]};
+          store_terms(reinterpret_cast<uintx4*>(A_op) + ((tile * q + mem) * NT + cb) * 128 + lane, operand_terms(anew[cb]));
       }
       // next iteration's A^T A: the new tile is at once the left and the right operand (rows on the K dimension)
       if constexpr (FUSE_G) {

@@ -211,7 +211,7 @@ nnrescal_status start_nndsvd_impl(nnrescal_handle* h, int svd_iters, int r_iters
   const int64_t ps = (int64_t)d.n * q * d.kp;       // one slice of P or Q
   const size_t kk = (size_t)k * k;
   // one slice's operand-order copy, with the spare member slots that a rounded-up tail group reads
-  const size_t op_stride = (size_t)d.n_pad * row + 8 * (size_t)d.kp * 16;
+  const size_t op_stride = kOperandFloats * ((size_t)d.n_pad * row + 8 * (size_t)d.kp * 16);
   nnrescal_status st = NNRESCAL_OK;
   float *Y = nullptr, *T1 = nullptr, *opP = nullptr, *opQ = nullptr, *gram = nullptr, *mat = nullptr, *coef = nullptr, *floor_d = nullptr;
   int* mode_d = nullptr;

@@ -1,0 +1,55 @@
+"""The dense pass over X keeps its fp32 operands as sums of three bf16 terms.  Both products of a slice against 64-bit
+products of the explicitly perturbed tensor (`nnrescal_perturb`, which the parity tests hold to the oracle bit for bit),
+member by member and column by column, at the edges of its tiles and panels (narrow and wide), for every way the elements
+are split (delta = 0, up to 1/16, above), with factors of both signs and columns and tensors of very different size.
+
+Bar per member and column, relative to the column's norm: the terms carry an operand to 2^-25 and the term products
+that are left out are below 2^-20 of a product, random in sign; the fp32 sums of n terms add about sqrt(n) 2^-24."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _check(lib, n, m, k, q, delta, deterministic=False, xscale=1.0, signs=False):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n * 131 + k)
+    X = torch.rand((m, n, n), generator=g, device=DEV) * xscale
+    A = torch.rand((q, n, k), generator=g, device=DEV) + 0.01
+    if signs:
+        A = A - 0.5
+    A = A * (2.0 ** torch.linspace(-30, 30, k, device=DEV))            # columns of very different size
+    R = torch.ones((q, m, k, k), device=DEV)
+    h = lib.nnrescal_init(lib.DenseX(X), k=k, q=q, delta=delta, seed=n, A0=A.contiguous(), R0=R, deterministic=deterministic)
+    tol = 2.0 ** -20 + n ** 0.5 * 2.0 ** -23
+    for t in range(m):
+        P, Q = lib.nnrescal_products(h, t)
+        for r in range(q):
+            Xr = lib.nnrescal_perturb(lib.DenseX(X), r, delta, n)[t].double() if delta > 0 else X[t].double()
+            a = A[r].double()
+            size = (Xr.abs() @ a.abs()).norm(dim=0), (Xr.abs().T @ a.abs()).norm(dim=0)
+            for got, want, scale in ((P[r], Xr @ a, size[0]), (Q[r], Xr.T @ a, size[1])):
+                err = ((got.double() - want).norm(dim=0) / scale).max().item()
+                assert err <= tol, (n, m, k, q, delta, t, r, err, tol)
+    lib.nnrescal_destroy(h)
+
+
+@pytest.mark.parametrize("n,m,k,q", [(1, 1, 1, 3), (1, 5, 1, 9), (2, 1, 2, 4), (3, 2, 3, 5), (15, 2, 4, 8), (17, 1, 16, 6),
+                                     (127, 2, 16, 11), (129, 1, 17, 7), (255, 1, 33, 3), (258, 2, 64, 2), (385, 1, 32, 3)])
+@pytest.mark.parametrize("delta", [0.0, 0.0625, 0.07, 0.9])
+def test_products_at_tile_edges(lib, n, m, k, q, delta):
+    _check(lib, n, m, k, q, delta)
+
+
+@pytest.mark.parametrize("n,k,q,delta,det", [(4097, 16, 7, 0.03, False), (4225, 5, 2, 0.5, False), (4099, 40, 1, 0.03, True),
+                                             (4096, 12, 1, 0.0, True)])
+def test_products_with_wide_panels(lib, n, k, q, delta, det):
+    _check(lib, n, 1, k, q, delta, deterministic=det)
+
+
+@pytest.mark.parametrize("xscale", [1e-30, 1e25])
+def test_products_range_and_signs(lib, xscale):
+    _check(lib, 200, 1, 16, 5, 0.03, xscale=xscale)
+    _check(lib, 200, 1, 20, 3, 0.03, xscale=xscale, signs=True)
