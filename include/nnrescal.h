@@ -306,7 +306,8 @@ NNRESCAL_API const char *nnrescal_last_error(const nnrescal_handle *h_or_null);
  * NULL), then switches profiling on (enable != 0: counters are reset) or off; enable == 2 times only the
  * passes over X and the A rule (classes 1, 2, 4 and 5), which perturbs a timed run less.  Classes follow the
  * paper's timing breakdown (section "Scalability"): 0 gram_mul (A^T A, A^T (X_t A)), 1 matrix_mul: the
- * dense pass over X for the groups of 8 members (one event pair = one kernel launch over all slices),
+ * dense pass over X for the groups of 8 members (4 for ranks 17 ... 32, 2 above; on small tensors for all
+ * members of an ensemble of at least that many; one event pair = one kernel launch over all slices),
  * 2 matrix_mul_sparse (with a CSC copy one pair per iteration: the launch that clears shared rows and the launch of
  * both products of all slices; without one, a pair for X_t A of all slices and one per slice for the scatter form of
  * X_t^T A), 3 element-wise and k x k update kernels,

@@ -111,7 +111,8 @@ hipError_t launch_pack_operand(const float* A_int, float* A_op, const Dims& d, h
 //                                 Q[t][j][r][:] = sum_i X[t][i][j] Delta^r[t][i][j] A[i][r][:].
 // P and Q must be zero on entry (partial sums are added atomically); the launcher does not clear them.
 // The members are taken in groups, each group's elements drawn from one Philox block.  part 0 = the members of whole groups
-// of 8 (4 for kp = 32, 2 above), part 1 = the others; a part with no members launches nothing.
+// of 8 (4 for kp = 32, 2 above; on small tensors all members, in one launch), part 1 = the others; a part with no members
+// launches nothing.
 struct DensePlan {
   int full_members, tail_members;
 };

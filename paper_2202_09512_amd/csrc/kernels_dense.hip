@@ -11,7 +11,7 @@
 // operand, built in registers by the lane that loaded the element; rows of the factor are the right operand, read from
 // a copy of A that is stored in operand order (two 16-byte loads per lane and product group).
 //
-// A workgroup of 8 waves owns a panel of 128 columns (8 tiles) and a chunk of rows.  In a round, every wave
+// A workgroup of W = 8 waves (4 on small tensors) owns a panel of 16 W columns (W tiles) and a chunk of rows.  In a round, every wave
 // takes one 16-row strip and walks it across the panel, tile by tile:
 //   - the strip's P accumulators and the right operands of the Q products (the strip's 16 factor rows) stay
 //     in registers for the whole strip; P is added to memory once per strip;
@@ -118,18 +118,18 @@ __device__ __forceinline__ u32x4 front_halves(u32x4 w, int hoff) {
 enum { kPlain = 0, kSharedHead = 1, kOwnHead = 2 };
 
 // Dynamic LDS layout (floats):
-//   [0, kWaves*NG*256)          panel-wide Q accumulator in MFMA accumulator order: qlds[tile][group][lane][4]
+//   [0, W*NG*256)          panel-wide Q accumulator in MFMA accumulator order: qlds[tile][group][lane][4]
 //   then per wave               transposition tiles of bf16 terms: 64 pieces of 8 bytes per
 //                               term, d1 and d2 of every member, then the head(s) x1
-//   then kWaves ints            completed steps per wave
-template <int NT, int QB, int MODE>
+//   then W ints            completed steps per wave
+template <int NT, int QB, int MODE, int W>
 struct StreamShape {
   static constexpr int NG = QB * NT;                            // product groups (member, 16-column block)
   static constexpr int NREST = MODE == kPlain ? 1 : QB;         // rests (d1, d2) per element
   static constexpr int NHEAD = MODE == kOwnHead ? QB : 1;       // heads (x1) per element
-  static constexpr int QLDS = kWaves * NG * 256;               // floats of the Q accumulator
+  static constexpr int QLDS = W * NG * 256;                    // floats of the Q accumulator
   static constexpr int TBUF = NREST * 256 + NHEAD * 128;        // floats of transposition space per wave
-  static constexpr size_t bytes = (size_t)(QLDS + kWaves * TBUF + kWaves) * sizeof(float);
+  static constexpr size_t bytes = (size_t)(QLDS + W * TBUF + W) * sizeof(float);
 };
 
 // four 16-bit values of one column of a row-major LDS tile (the 16 lanes of a group each address four of a row)
@@ -139,15 +139,15 @@ __device__ __forceinline__ uintx2 read_transposed(const void* lds_ptr) {
                                         (__attribute__((address_space(3))) s4*)(__attribute__((address_space(3))) void*)lds_ptr));
 }
 
-template <int NT, int QB, int MODE>
-__global__ void __launch_bounds__(kWaves * 64)
+template <int NT, int QB, int MODE, int W>
+__global__ void __launch_bounds__(W * 64, 2)
     dense_stream_kernel(const float* __restrict__ X, const uintx4* __restrict__ A_op, float* __restrict__ P,
                         float* __restrict__ Q, int64_t n, int m, int q, int k, int qfirst, int ngroups, int n_chunks,
                         int64_t rows_per_chunk, uint32_t k0, uint32_t k1, float dscaled, int t_first,
                         const uintx4* __restrict__ A_opQ, int64_t aop_tstride, int64_t out_tstride,
                         int32_t* __restrict__ timeout_flag, int spin_limit, float* __restrict__ Ppart,
                         int64_t ppart_stride) {
-  typedef StreamShape<NT, QB, MODE> Shape;
+  typedef StreamShape<NT, QB, MODE, W> Shape;
   constexpr int NG = Shape::NG, NREST = Shape::NREST, NHEAD = Shape::NHEAD;
   extern __shared__ __attribute__((aligned(16))) float lds[];
   float* qlds = lds;
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int l16 = lane & 15, row = lane >> 4;
   char* tbuf = reinterpret_cast<char*>(lds + Shape::QLDS + wave * Shape::TBUF);
   // done[w]: number of steps wave w has completed (see the hand-over of the tile columns below)
-  int* done = reinterpret_cast<int*>(lds + Shape::QLDS + kWaves * Shape::TBUF);
+  int* done = reinterpret_cast<int*>(lds + Shape::QLDS + W * Shape::TBUF);
   if (lane == 0) done[wave] = 0;
 
   // Workgroups are handed to the 8 XCDs round-robin; give each XCD a contiguous range of logical indices.  Member group
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   const int qb = (q - q0) < QB ? (q - q0) : QB;
   const uint32_t sub = (uint32_t)(q0 >> 3);         // Philox block index of this member group
   const int hoff = QB == 8 ? 0 : (q0 & 7);          // first 16-bit half used by the group
-  const int64_t jp0 = (int64_t)panel * kPanel;
+  const int64_t jp0 = (int64_t)panel * (16 * W);
   const int64_t i_begin = (int64_t)chunk * rows_per_chunk;
   int64_t i_end = i_begin + rows_per_chunk;
   if (i_end > n) i_end = n;
@@ -190,10 +190,10 @@ __global__ void __launch_bounds__(kWaves * 64)
   float* Qt = Q + (int64_t)t * out_tstride;
   const int n32 = (int)n;
   int tiles = (int)((n - jp0 + 15) >> 4);           // tiles of the panel that hold columns of the matrix
-  if (tiles > kWaves) tiles = kWaves;
-  const int cols = (int)(n - jp0 < kPanel ? n - jp0 : kPanel);   // columns of the panel
+  if (tiles > W) tiles = W;
+  const int cols = (int)(n - jp0 < 16 * W ? n - jp0 : 16 * W);   // columns of the panel
 
-  for (int e = tid; e < Shape::QLDS; e += kWaves * 64) qlds[e] = 0.0f;
+  for (int e = tid; e < Shape::QLDS; e += W * 64) qlds[e] = 0.0f;
   __syncthreads();
 
   // Operand address of (tile of 16 entities, product group g), in units of 16 bytes: a wave-uniform part
@@ -210,18 +210,11 @@ __global__ void __launch_bounds__(kWaves * 64)
   // wave w + 1 to wave w; instead of a barrier per step each wave counts its completed steps in LDS and waits
   // only for the one wave it takes its column from.
   const int nstrips = (int)((i_end - i_begin + 15) >> 4);
-  const int nrounds = (nstrips + kWaves - 1) / kWaves;
-  auto tile_of = [&](int s) { return (wave + s) & (kWaves - 1); };
+  const int nrounds = (nstrips + W - 1) / W;
+  auto tile_of = [&](int s) { return (wave + s) & (W - 1); };
   // first row of this wave's strip in round rnd (a wave without a strip, or past the last round, reads the
   // chunk's first strip: valid memory, never used)
-  // The workgroups of one chunk (one per panel) add to the same rows of P; each starts at a different round so
-  // that they do not meet on the same rows at the same time.
-  const int rnd0 = panel % nrounds;
-  auto strip_of = [&](int rnd) -> int {
-    int rr = rnd + rnd0;
-    if (rr >= nrounds) rr -= nrounds;
-    return rr * kWaves + wave;
-  };
+  auto strip_of = [&](int rnd) -> int { return rnd * W + wave; };
   auto strip_row = [&](int rnd) -> int64_t {
     const int strip = rnd < nrounds ? strip_of(rnd) : nstrips;
     return i_begin + 16 * (int64_t)(strip < nstrips ? strip : 0);
@@ -262,7 +255,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   // (one plain store by lane 0), leaves the Q half of that step out (the column may still be its neighbour's) and
   // goes on counting, so that the kernel exits normally; the host turns the flag into an error status.
   auto wait_for_neighbour = [&](int gstep) -> bool {
-    const int nb = (wave + 1) & (kWaves - 1);
+    const int nb = (wave + 1) & (W - 1);
     bool arrived = false;
     for (int spin = 0; spin < spin_limit; ++spin) {
       const int c = __builtin_amdgcn_readfirstlane(
@@ -303,7 +296,7 @@ __global__ void __launch_bounds__(kWaves * 64)
       const int jt = tile_of(s);
       const bool work = have_strip && jt < tiles;   // wave-uniform
       floatx4 xc = x;
-      x = x_fetch(s + 2 < kWaves ? i0 : i0_next, tile_of(s + 2));
+      x = x_fetch(s + 2 < W ? i0 : i0_next, tile_of(s + 2));
       if (work) {
         if (rows_left < 16 || 16 * jt + 16 > cols) {          // wave-uniform
           xc = take_tile(xc, rows_left - l16, cols - (16 * jt + 4 * row));
@@ -379,7 +372,7 @@ __global__ void __launch_bounds__(kWaves * 64)
       }
       __builtin_amdgcn_s_setprio(kPrioRest);
       // the operand registers are free again: fetch the next tile's
-      bp_fetch(tile_of((s + 1) & (kWaves - 1)));
+      bp_fetch(tile_of((s + 1) & (W - 1)));
       if (work) {
         // ---- "column" orientation read back from LDS: lane (l16, row) gets the terms of rows i0 + 4*row + r of column
         //      j0 + l16; the tile's Q accumulators are this wave's alone until the next barrier
@@ -387,7 +380,7 @@ __global__ void __launch_bounds__(kWaves * 64)
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         // Tile column jt was wave (wave + 1) % 8's in the previous step: wait until that wave has completed it.
-        const bool mine = wait_for_neighbour(rnd * kWaves + s);   // wave-uniform
+        const bool mine = wait_for_neighbour(rnd * W + s);   // wave-uniform
         float4* qt = reinterpret_cast<float4*>(qlds) + (jt * NG) * 64 + lane;
         // QH members at a time: all LDS reads first (one wait), then the products back to back, then the stores (with all
         // 8 groups at a time the registers run out; halves spill 8 and are 2 % slower than quarters at n = 16384)
@@ -433,17 +426,17 @@ __global__ void __launch_bounds__(kWaves * 64)
         // A wave with nothing to do in this step (no strip in the chunk's last round, or a tile beyond the matrix)
         // still is a link of the chain: its count may move only after its neighbour's, or the wave behind it
         // could take the column over while the wave in front is still working on it.
-        (void)wait_for_neighbour(rnd * kWaves + s);
+        (void)wait_for_neighbour(rnd * W + s);
       }
       // the strip's last Q products are done: fetch the next strip's operands behind them
-      if (s == kWaves - 1 && rnd + 1 < nrounds) bq_fetch(rnd + 1);
+      if (s == W - 1 && rnd + 1 < nrounds) bq_fetch(rnd + 1);
       // hand the tile column on: the accumulators are in LDS before the count moves
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0)
-        __hip_atomic_store(&done[wave], rnd * kWaves + s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&done[wave], rnd * W + s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
 #pragma unroll 1
-    for (int s = 0; s < kWaves; s += 2) {           // (two steps per trip: the two tiles in flight keep their registers)
+    for (int s = 0; s < W; s += 2) {           // (two steps per trip: the two tiles in flight keep their registers)
       step(s, xeven);
       step(s + 1, xodd);
     }
@@ -471,7 +464,7 @@ __global__ void __launch_bounds__(kWaves * 64)
   __syncthreads();
   // ---- the panel's Q (summed over the chunk's rows): add to memory (every wave has made its last step)
   constexpr int kp = 16 * NT;
-  for (int e = tid; e < tiles * NG * 256; e += kWaves * 64) {
+  for (int e = tid; e < tiles * NG * 256; e += W * 64) {
     const float v = qlds[e];
     const int r = e & 3, ln = (e >> 2) & 63, g = (e >> 8) % NG, jt = (e >> 8) / NG;
     const int qq = g / NT, nt = g % NT;
@@ -486,7 +479,7 @@ __global__ void __launch_bounds__(kWaves * 64)
 
 const char* dense_stream_kernel_name() { return "dense_stream_kernel"; }
 
-template <int NT, int QB, int MODE>
+template <int NT, int QB, int MODE, int W>
 static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qfirst,
                                   int ngroups, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   const int t_first = o.t_first;
@@ -498,25 +491,25 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
   const int64_t ppart_stride = (int64_t)d.m * d.n * d.q * d.kp;   // one copy of P per panel
   if (Ppart && out_tstride != d.n * d.q * (int64_t)d.kp) return hipErrorInvalidValue;   // (not with summed slices)
   static_assert(QB * NT <= 8, "at most 8 product groups per tile");
-  constexpr size_t lds = StreamShape<NT, QB, MODE>::bytes;
+  constexpr size_t lds = StreamShape<NT, QB, MODE, W>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, MODE>,
+    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, MODE, W>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int64_t n_panels = ceil_div(d.n, kPanel);
+  const int64_t n_panels = ceil_div(d.n, 16 * W);
   // Rows are cut into chunks (whole rounds of 8 strips = 128 rows) so that the 256 CUs, one workgroup each at a
   // time, are busy: more chunks even out the last wave of workgroups, fewer chunks save the fixed cost of a
   // workgroup (clearing and adding out its share of Q, filling its pipeline: about 7 steps, i.e. the time of
   // ~112 rows, measured).  Pick the count with the least estimated time.
   const int64_t base = n_panels * d.m * ngroups;
-  const int64_t max_chunks = ceil_div(d.n, kPanel);
+  const int64_t max_chunks = ceil_div(d.n, 16 * W);
   int64_t n_chunks = 1, best = -1;
   for (int64_t c = 1; c <= max_chunks && c <= 256; ++c) {
-    const int64_t rows = round_up(ceil_div(d.n, c), kPanel);
+    const int64_t rows = round_up(ceil_div(d.n, c), 16 * W);
     const int64_t waves_of_wgs = ceil_div(base * ceil_div(d.n, rows), 256);
     // (a single wave of workgroups measured 20 % slower than two of half the length: nothing overlaps its ends)
     const int64_t cost = waves_of_wgs * (rows + 112) * (waves_of_wgs == 1 ? 5 : 4);
@@ -526,11 +519,11 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
     }
   }
   if (Ppart) n_chunks = 1;                          // one workgroup per panel and slice: the only writer of its X_t^T A
-  const int64_t rows_per_chunk = round_up(ceil_div(d.n, n_chunks), kPanel);
+  const int64_t rows_per_chunk = round_up(ceil_div(d.n, n_chunks), 16 * W);
   n_chunks = ceil_div(d.n, rows_per_chunk);
   const int64_t total = n_panels * n_chunks * d.m * ngroups;
   if (total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_stream_kernel<NT, QB, MODE>), dim3((unsigned)total), dim3(kWaves * 64), lds, s, X,
+  hipLaunchKernelGGL((dense_stream_kernel<NT, QB, MODE, W>), dim3((unsigned)total), dim3(W * 64), lds, s, X,
                      (const uintx4*)A_op, P, Q, d.n, d.m, d.q, d.k, qfirst, ngroups, (int)n_chunks, rows_per_chunk,
                      (uint32_t)seed, (uint32_t)(seed >> 32), delta * 0x1p-16f, t_first, (const uintx4*)A_opQ,
                      o.aop_tstride / 4, out_tstride, timeout_flag, spin_limit, Ppart, ppart_stride);
@@ -550,40 +543,76 @@ static int group_members(int kp) { return kp <= 16 ? 8 : (kp <= 32 ? 4 : 2); }
 
 int64_t dense_stream_panels(const Dims& d) { return ceil_div(d.n, kPanel); }
 
+// How a pass is cut into workgroups.  The big groups share the generator among the most members; a tensor whose blocks of
+// 128 x 128 elements, times groups, do not fill the 256 compute units has its time decided by the length of one
+// workgroup's chain of steps instead: it takes smaller groups (all members, a last group with empty slots included, in
+// one launch) and at last workgroups of 4 waves on blocks of 64 x 64.  Per pass, n / slices / members at rank <= 16,
+// big groups and tail -> the form taken here (us):
+//   4 waves, groups of 1:  100 / 2 / 4   21.7 -> 10.4     (of 2: 11.7)
+//   4 waves, groups of 2:  250 / 3 / 10  50.4 -> 13.4     (of 1: 15.4; 8 waves 18.2)
+//   8 waves, groups of 2:  333 / 5 / 10  49.6 -> 18.6     500 / 6 / 10  52.0 -> 29.5    (4 waves 20.6 and 33; of 4: 23.4 and 36.5)
+//   8 waves, groups of 4:  512 / 8 / 16  52.4 -> 46.4     (of 2: 48.5); with a tail, whose launch is saved,
+//                          1024 / 10 / 10  132 -> 125     2048 / 4 / 10  195 -> 185
+// and beyond: 1501 / 4 / 8 big groups 89, groups of 4 98; 2048 / 8 / 10 309 and 351.  (Rank 24 alike, with half the members
+// per group: 333 / 5 / 10 53.6 -> 26, 1024 / 4 / 10 106 -> 99.)
+struct StreamForm {
+  int waves, members;
+  bool merged;                                      // all members in one launch
+};
+static StreamForm stream_form(const Dims& d) {
+  const int big = group_members(d.kp), nt = d.kp / 16;
+  const auto blocks = [&](int side, int members) { return ceil_div(d.n, side) * ceil_div(d.n, side) * d.m * ceil_div(d.q, members); };
+  const int two = nt == 1 ? 2 : 1, four = nt == 1 ? 4 : (nt == 2 ? 2 : 1);
+  if (blocks(64, 1) <= 256) return {4, 1, true};
+  if (blocks(64, two) <= 512) return {4, two, true};
+  if (blocks(kPanel, two) <= 512 && nt <= 2) return {kWaves, two, true};
+  const int64_t b = blocks(kPanel, big);
+  if ((b <= 256 && nt <= 2) || (b <= 2048 && d.q % big != 0)) return {kWaves, four, true};
+  return {kWaves, big, false};
+}
+
 DensePlan dense_stream_plan(const Dims& d) {
   const int big = group_members(d.kp);
+  if (d.q >= big && stream_form(d).merged) return DensePlan{d.q, 0};
   return DensePlan{d.q / big * big, d.q % big};
 }
 
-template <int NT, int QB>
+template <int NT, int QB, int W>
 static hipError_t launch_stream_qb(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int ngroups,
                                    uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  if constexpr (QB * NT <= 8) {
+  if constexpr (QB * NT <= 8 && (W == kWaves || QB * NT <= (NT > 2 ? NT : 2))) {
     switch (split_mode(delta)) {
-      case kPlain: return launch_stream_t<NT, QB, kPlain>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
-      case kSharedHead: return launch_stream_t<NT, QB, kSharedHead>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+      case kPlain: return launch_stream_t<NT, QB, kPlain, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+      case kSharedHead: return launch_stream_t<NT, QB, kSharedHead, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
       default:
-        if constexpr (QB <= 4) return launch_stream_t<NT, QB, kOwnHead>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
+        if constexpr (QB <= 4) return launch_stream_t<NT, QB, kOwnHead, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
     }
   }
   return hipErrorInvalidValue;
 }
 
-// Members [qf, qf + count): whole groups in one launch, a rest in one of a group rounded up to a power of two.
+// Members [qf, qf + count): whole groups in one launch, a rest in one of a group rounded up to a power of two; merged: all in
+// one launch.
 template <int NT>
 static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int count,
                                    uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  int qb = group_members(d.kp);
+  const StreamForm f = stream_form(d);
+  int qb = f.members;
   if (split_mode(delta) == kOwnHead && qb > 4) qb = 4;   // (8 members' transposition tiles with their heads exceed the LDS)
+  if (f.merged) count = (int)round_up(count, qb);
+  if (f.waves == 4 && !o.Ppart) {                   // (the reproducible mode's copies of P are one per 128 columns)
+    return qb == 1 ? launch_stream_qb<NT, 1, 4>(X, A_op, P, Q, d, qf, count, seed, delta, s, o)
+                   : launch_stream_qb<NT, 2, 4>(X, A_op, P, Q, d, qf, count / 2, seed, delta, s, o);
+  }
   hipError_t e = hipSuccess;
   while (count > 0 && e == hipSuccess) {
     while (qb / 2 >= count) qb /= 2;
     const int groups = count < qb ? 1 : count / qb;
     switch (qb) {
-      case 1: e = launch_stream_qb<NT, 1>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      case 2: e = launch_stream_qb<NT, 2>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      case 4: e = launch_stream_qb<NT, 4>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      default: e = launch_stream_qb<NT, 8>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      case 1: e = launch_stream_qb<NT, 1, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      case 2: e = launch_stream_qb<NT, 2, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      case 4: e = launch_stream_qb<NT, 4, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
+      default: e = launch_stream_qb<NT, 8, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
     }
     qf += groups * qb;
     count -= groups * qb;
@@ -595,6 +624,7 @@ hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, floa
                                uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   const DensePlan pl = dense_stream_plan(d);
   const int qf = part == 0 ? 0 : pl.full_members, count = part == 0 ? pl.full_members : pl.tail_members;
+  if (count == 0) return hipSuccess;
   switch (d.kp / 16) {
     case 1: return launch_stream_nt<1>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
     case 2: return launch_stream_nt<2>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);

@@ -53,3 +53,12 @@ def test_products_with_wide_panels(lib, n, k, q, delta, det):
 def test_products_range_and_signs(lib, xscale):
     _check(lib, 200, 1, 16, 5, 0.03, xscale=xscale)
     _check(lib, 200, 1, 20, 3, 0.03, xscale=xscale, signs=True)
+
+
+# one size for each way a pass is cut into workgroups: 4 waves with groups of 1 and of 2 members, 8 waves with groups of 2 and
+# of 4 (a last group with empty slots among them) and with the largest groups, without and with a tail
+@pytest.mark.parametrize("n,m,k,q", [(100, 2, 8, 4), (250, 3, 10, 9), (333, 5, 8, 9), (333, 5, 24, 9), (500, 8, 3, 15),
+                                     (600, 4, 24, 9), (600, 4, 40, 5), (600, 7, 16, 16), (1501, 8, 3, 9)])
+@pytest.mark.parametrize("delta", [0.0, 0.03, 0.5])
+def test_products_in_every_form(lib, n, m, k, q, delta):
+    _check(lib, n, m, k, q, delta)
