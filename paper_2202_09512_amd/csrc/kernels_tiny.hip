@@ -4,58 +4,75 @@
 // of the general path is ten kernel launches of a few microseconds each: launch latency, not arithmetic.
 //
 // Same statements as the general path (the n-sized products re-associated the same way), each batched over the
-// slices (the R updates of different slices are independent once G is known), so that an iteration costs seven
+// slices (the R updates of different slices are independent once G is known), so that an iteration costs six
 // barriers:
 //   G = A^T A;  P_t = X_t A, Q_t = X_t^T A;  S_t = A^T P_t;  R_t <- R_t (*) S_t (/) (G R_t G + eps);
 //   Num = sum_t P_t R_t^T + Q_t R_t;  W = sum_t R_t G R_t^T + R_t^T G R_t;  A <- A (*) Num (/) (A W + eps).
+//
+// The k x k sums are formed in 64 bits, which costs nothing here: their roundings are common to all entities, and over
+// hundreds of iterations they add up along the factors' common scale.
+// What bounds it: LDS reads and their latency on ONE compute unit per member.  So a workgroup has as many waves as a
+// compute unit holds, the sums are split over neighbouring lanes (4 for the n-long ones of P and Q, 16 for those of the
+// k x k matrices) and added up by lane permutations, a lane of the products takes a row of X for P and the column of the
+// same number for Q, which need the same rows of A, and it takes 4 columns of A in one read: 8 multiply-adds for three
+// reads.  Per iteration (64 entities, 4 slices, rank 3): 14.6 -> 4.7 us.
 #include "common.h"
 #include "kernels.h"
 
 namespace nnr {
 
-constexpr int kTinyThreads = 256;
-constexpr int kTinyMaxN = 64;                        // the A rule stages its new elements in registers
+constexpr int kTinyThreads = 1024;
+constexpr int kTinyMaxN = 64;
 
-// out[a*cols + b] = sum_{c < len} term(a, b, c).  Four independent partial sums per element keep several LDS
-// reads in flight (these loops are bound by LDS latency, not by arithmetic).
-template <typename F>
-__device__ __forceinline__ void sum_terms(float* out, int rows, int cols, int len, F term) {
-  for (int e = threadIdx.x; e < rows * cols; e += kTinyThreads) {
-    const int a = e / cols, b = e % cols;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    int c = 0;
-    for (; c + 4 <= len; c += 4) {
-      s0 += term(a, b, c);
-      s1 += term(a, b, c + 1);
-      s2 += term(a, b, c + 2);
-      s3 += term(a, b, c + 3);
-    }
-    for (; c < len; ++c) s0 += term(a, b, c);
-    out[e] = (s0 + s1) + (s2 + s3);
-  }
+// sums over 4 and over 16 neighbouring lanes, all of which take part (the result is in every one of them)
+template <int CTRL>
+__device__ __forceinline__ float add_permuted(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float quad_sum(float v) { return add_permuted<0x4E>(add_permuted<0xB1>(v)); }   // lane ^ 1, lane ^ 2
+template <int CTRL>
+__device__ __forceinline__ double add_permuted(double v) {
+  return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false),
+                              __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double row_sum(double v) {
+  return add_permuted<0x140>(add_permuted<0x141>(add_permuted<0x4E>(add_permuted<0xB1>(v))));   // ..., mirrored 8, mirrored 16
 }
 
+// Divisor of indices below 2^20 that is not known at compile time: (e + 1/2) / v is at least 1 / (2 v) away from an integer,
+// more than the two roundings move it.
+struct SmallDiv {
+  int v;
+  float inv;
+  __device__ explicit SmallDiv(int d) : v(d), inv(1.0f / (float)d) {}
+  __device__ int div(int e) const { return (int)(((float)e + 0.5f) * inv); }
+};
+
+// CK: columns of A that a lane reads at once; the pitch of n x k arrays is k rounded up to a multiple of it (the spare
+// columns are zero and stay zero)
+template <int CK>
 __global__ void __launch_bounds__(kTinyThreads)
     tiny_fit_kernel(const float* __restrict__ X, float* __restrict__ A_int, float* __restrict__ R, Dims d, int iters,
                     float eps, uint32_t k0, uint32_t k1, float dscaled, int perturb) {
-  extern __shared__ float lds[];
-  const int n = (int)d.n, m = d.m, k = d.k, q = d.q, kp = d.kp, kk = k * k;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int n = (int)d.n, m = d.m, k = d.k, q = d.q, kp = d.kp, kk = k * k, mn = m * n, mkk = m * kk;
+  const int kc = (k + CK - 1) / CK * CK, tid = threadIdx.x;
   const int r = blockIdx.x;                          // ensemble member
   const int ldx = n + 1;                             // row pitch of a slice: column walks stay conflict-free
   float* Xs = lds;                                   // [m][n][ldx]
-  float* As = Xs + (size_t)m * n * ldx;              // [n][k]
-  float* Pa = As + n * k;                            // [m][n][k]: X_t A
-  float* Qa = Pa + (size_t)m * n * k;                // [m][n][k]: X_t^T A
-  float* Num = Qa + (size_t)m * n * k;               // [n][k]
-  float* Rs = Num + n * k;                           // [m][k][k]
-  float* Sa = Rs + m * kk;                           // [m][k][k]: A^T X_t A
-  float* T1 = Sa + m * kk;                           // [m][k][k]
-  float* T2 = T1 + m * kk;                           // [m][k][k]
-  float* Gs = T2 + m * kk;                           // [k][k]
+  float* As = Xs + ((mn * ldx + 3) & ~3);            // [n][kc]
+  float* Num = As + n * kc;                          // [n][kc]
+  float* Pa = Num + n * kc;                          // [m][n][kc]: X_t A
+  float* Qa = Pa + mn * kc;                          // [m][n][kc]: X_t^T A
+  float* Rs = Qa + mn * kc;                          // [m][k][k]
+  float* Sa = Rs + mkk;                              // [m][k][k]: A^T X_t A
+  float* T1 = Sa + mkk;                              // [m][k][k]
+  float* T2 = T1 + mkk;                              // [m][k][k]
+  float* Gs = T2 + mkk;                              // [k][k]
   float* Ws = Gs + kk;                               // [k][k]
 
   // ---- the member's perturbed tensor (one Philox block per element; this member's 16-bit half of it)
-  for (int e = threadIdx.x; e < m * n * n; e += kTinyThreads) {
+  for (int e = tid; e < mn * n; e += kTinyThreads) {
     const int t = e / (n * n), i = (e / n) % n, j = e % n;
     float v = X[e];
     if (perturb) {
@@ -63,82 +80,171 @@ __global__ void __launch_bounds__(kTinyThreads)
       const u32x4 w = philox4x32_10((uint32_t)c, (uint32_t)(c >> 32), (uint32_t)t, (uint32_t)(r >> 3), k0, k1);
       v = perturbed(v, w, r & 7, dscaled);
     }
-    Xs[((size_t)t * n + i) * ldx + j] = v;
+    Xs[(t * n + i) * ldx + j] = v;
   }
-  for (int e = threadIdx.x; e < n * k; e += kTinyThreads) As[e] = A_int[((int64_t)(e / k) * q + r) * kp + e % k];
-  for (int e = threadIdx.x; e < m * kk; e += kTinyThreads) Rs[e] = R[(int64_t)r * m * kk + e];
+  for (int e = tid; e < n * kc; e += kTinyThreads) {
+    const int i = e / kc, c = e % kc;
+    As[e] = c < k ? A_int[((int64_t)i * q + r) * kp + c] : 0.0f;
+    Num[e] = 0.0f;
+  }
+  for (int e = tid; e < mkk; e += kTinyThreads) Rs[e] = R[(int64_t)r * mkk + e];
   __syncthreads();
 
+  const int part = tid & 3, l16 = tid & 15, rtid = kTinyThreads - 1 - tid;   // (short work starts at the last threads)
+  const SmallDiv by_k(k), by_n(n), by_mn(mn);
+  const int j0 = part * ((n + 3) >> 2), j1 = j0 + ((n + 3) >> 2) < n ? j0 + ((n + 3) >> 2) : n;
+  // (the quarters are read from different places on: rows of A a quarter of n apart would often share their banks)
+  const int jfirst = j0 < j1 ? j0 + part % (j1 - j0) : j0;
   for (int it = 0; it < iters; ++it) {
-    // G[a][b] = sum_i A[i][a] A[i][b];  P[(t,i)][c] = sum_j X_t[i][j] A[j][c];  Q[(t,j)][c] = sum_i X_t[i][j] A[i][c]
-    sum_terms(Gs, k, k, n, [&](int a, int b, int i) { return As[i * k + a] * As[i * k + b]; });
-    sum_terms(Pa, m * n, k, n, [&](int ti, int c, int j) { return Xs[(size_t)ti * ldx + j] * As[j * k + c]; });
-    sum_terms(Qa, m * n, k, n,
-              [&](int tj, int c, int i) { return Xs[((size_t)(tj / n) * n + i) * ldx + tj % n] * As[i * k + c]; });
-    __syncthreads();
-    // S[(t,a)][b] = sum_i A[i][a] P_t[i][b];  T1[(t,a)][b] = sum_c R_t[a][c] G[c][b]
-    sum_terms(Sa, m * k, k, n, [&](int ta, int b, int i) { return As[i * k + ta % k] * Pa[((ta / k) * n + i) * k + b]; });
-    sum_terms(T1, m * k, k, k, [&](int ta, int b, int c) { return Rs[ta * k + c] * Gs[c * k + b]; });
-    __syncthreads();
-    // T2[(t,a)][b] = sum_c G[a][c] T1_t[c][b] = (G R_t G)[a][b]
-    sum_terms(T2, m * k, k, k, [&](int ta, int b, int c) { return Gs[(ta % k) * k + c] * T1[((ta / k) * k + c) * k + b]; });
-    __syncthreads();
-    for (int e = threadIdx.x; e < m * kk; e += kTinyThreads) Rs[e] = Rs[e] * Sa[e] / (T2[e] + eps);
-    __syncthreads();
-    // with the new R_t: T1_t = G R_t^T, T2_t = G R_t;
-    // Num[i][c] = sum_{(t,b)} P_t[i][b] R_t[c][b] + Q_t[i][b] R_t[b][c]
-    sum_terms(T1, m * k, k, k, [&](int ta, int b, int c) { return Gs[(ta % k) * k + c] * Rs[((ta / k) * k + b) * k + c]; });
-    sum_terms(T2, m * k, k, k, [&](int ta, int b, int c) { return Gs[(ta % k) * k + c] * Rs[((ta / k) * k + c) * k + b]; });
-    sum_terms(Num, n, k, m * k, [&](int i, int c, int tb) {
-      const int t = tb / k, b = tb % k;
-      return Pa[(t * n + i) * k + b] * Rs[(t * k + c) * k + b] + Qa[(t * n + i) * k + b] * Rs[(t * k + b) * k + c];
-    });
-    __syncthreads();
-    // W[a][b] = sum_{(t,c)} R_t[a][c] (G R_t^T)[c][b] + R_t[c][a] (G R_t)[c][b]
-    sum_terms(Ws, k, k, m * k, [&](int a, int b, int tc) {
-      const int t = tc / k, c = tc % k;
-      return Rs[(t * k + a) * k + c] * T1[(t * k + c) * k + b] + Rs[(t * k + c) * k + a] * T2[(t * k + c) * k + b];
-    });
-    __syncthreads();
-    // A <- A (*) Num (/) (A W + eps): every thread forms its own elements from the old A first
-    float newa[(kTinyMaxN * NNRESCAL_MAX_K_INTERNAL + kTinyThreads - 1) / kTinyThreads];
-    int cnt = 0;
-    for (int e = threadIdx.x; e < n * k; e += kTinyThreads, ++cnt) {
-      const int i = e / k, c = e % k;
-      float den = 0.0f;
-      for (int b = 0; b < k; ++b) den = fmaf(As[i * k + b], Ws[b * k + c], den);
-      newa[cnt] = As[e] * Num[e] / (den + eps);
+    // P[(t,i)][c] = sum_j X_t[i][j] A[j][c];  Q[(t,i)][c] = sum_j X_t[j][i] A[j][c]: a quarter of the j per lane
+    for (int e = tid >> 2; e < mn * (kc / CK); e += kTinyThreads / 4) {
+      const int ch = by_mn.div(e), c0 = ch * CK, ti = e - ch * mn, t = by_n.div(ti);
+      const float* xrow = Xs + ti * ldx;
+      const float* xcol = Xs + t * n * ldx + (ti - t * n);
+      float p[CK], y[CK];
+#pragma unroll
+      for (int u = 0; u < CK; ++u) p[u] = y[u] = 0.0f;
+      int j = jfirst;
+#pragma unroll 4
+      for (int jj = j0; jj < j1; ++jj) {
+        float a[CK];
+        if constexpr (CK == 4) {
+          const float4 v = *reinterpret_cast<const float4*>(As + j * kc + c0);
+          a[0] = v.x; a[1] = v.y; a[2] = v.z; a[3] = v.w;
+        } else {
+          a[0] = As[j * kc + c0];
+        }
+        const float xr = xrow[j], xc = xcol[j * ldx];
+#pragma unroll
+        for (int u = 0; u < CK; ++u) {
+          p[u] = fmaf(xr, a[u], p[u]);
+          y[u] = fmaf(xc, a[u], y[u]);
+        }
+        j = j + 1 < j1 ? j + 1 : j0;
+      }
+#pragma unroll
+      for (int u = 0; u < CK; ++u) {
+        const float ps = quad_sum(p[u]), ys = quad_sum(y[u]);
+        if (part == 0) Pa[ti * kc + c0 + u] = ps;
+        if (part == 1) Qa[ti * kc + c0 + u] = ys;
+      }
+    }
+    // G[a][b] = sum_i A[i][a] A[i][b]
+    for (int e = rtid >> 4; e < kk; e += kTinyThreads / 16) {
+      const int a = by_k.div(e), b = e - a * k;
+      double s = 0.0;
+      for (int i = l16; i < n; i += 16) s = fma((double)As[i * kc + a], (double)As[i * kc + b], s);
+      s = row_sum(s);
+      if (l16 == 0) Gs[e] = (float)s;
     }
     __syncthreads();
-    cnt = 0;
-    for (int e = threadIdx.x; e < n * k; e += kTinyThreads, ++cnt) As[e] = newa[cnt];
+    // S[(t,a)][b] = sum_i A[i][a] P_t[i][b];  T1[(t,a)][b] = sum_c R_t[a][c] G[c][b]
+    for (int e = tid >> 4; e < mkk; e += kTinyThreads / 16) {
+      const int ta = by_k.div(e), b = e - ta * k, t = by_k.div(ta), a = ta - t * k;
+      double s = 0.0;
+      for (int i = l16; i < n; i += 16) s = fma((double)As[i * kc + a], (double)Pa[(t * n + i) * kc + b], s);
+      s = row_sum(s);
+      if (l16 == 0) Sa[e] = (float)s;
+    }
+    for (int e = rtid; e < mkk; e += kTinyThreads) {
+      const int ta = by_k.div(e), b = e - ta * k;
+      float s = 0.0f;
+      for (int c = 0; c < k; ++c) s = fmaf(Rs[ta * k + c], Gs[c * k + b], s);
+      T1[e] = s;
+    }
     __syncthreads();
+    // R_t <- R_t (*) S_t (/) (G R_t G + eps), (G R_t G)[a][b] = sum_c G[a][c] T1_t[c][b]
+    for (int e = tid; e < mkk; e += kTinyThreads) {
+      const int ta = by_k.div(e), b = e - ta * k, t = by_k.div(ta), a = ta - t * k;
+      double s = 0.0;
+      for (int c = 0; c < k; ++c) s = fma((double)Gs[a * k + c], (double)T1[(t * k + c) * k + b], s);
+      Rs[e] = Rs[e] * Sa[e] / ((float)s + eps);
+    }
+    __syncthreads();
+    // with the new R_t: Num[i][c] = sum_{(t,b)} P_t[i][b] R_t[c][b] + Q_t[i][b] R_t[b][c], a quarter of the t per lane;
+    // T1_t = G R_t^T, T2_t = G R_t
+    for (int e = tid >> 2; e < n * k; e += kTinyThreads / 4) {
+      const int i = by_k.div(e), c = e - i * k;
+      float s = 0.0f;
+      for (int t = part; t < m; t += 4) {
+        const float *p = Pa + (t * n + i) * kc, *y = Qa + (t * n + i) * kc, *rt = Rs + t * kk;
+        for (int b = 0; b < k; ++b) s = fmaf(y[b], rt[b * k + c], fmaf(p[b], rt[c * k + b], s));
+      }
+      s = quad_sum(s);
+      if (part == 0) Num[i * kc + c] = s;
+    }
+    for (int e = rtid; e < mkk; e += kTinyThreads) {
+      const int ta = by_k.div(e), b = e - ta * k, t = by_k.div(ta), a = ta - t * k;
+      float s1 = 0.0f, s2 = 0.0f;
+      for (int c = 0; c < k; ++c) {
+        const float g = Gs[a * k + c];
+        s1 = fmaf(g, Rs[(t * k + b) * k + c], s1);
+        s2 = fmaf(g, Rs[(t * k + c) * k + b], s2);
+      }
+      T1[e] = s1;
+      T2[e] = s2;
+    }
+    __syncthreads();
+    // W[a][b] = sum_{(t,c)} R_t[a][c] (G R_t^T)[c][b] + R_t[c][a] (G R_t)[c][b]
+    for (int e = tid >> 4; e < kk; e += kTinyThreads / 16) {
+      const int a = by_k.div(e), b = e - a * k;
+      double s = 0.0;
+      for (int tc = l16; tc < m * k; tc += 16) {
+        const int t = by_k.div(tc), c = tc - t * k;
+        s = fma((double)Rs[(t * k + c) * k + a], (double)T2[tc * k + b],
+                fma((double)Rs[(t * k + a) * k + c], (double)T1[tc * k + b], s));
+      }
+      s = row_sum(s);
+      if (l16 == 0) Ws[e] = (float)s;
+    }
+    __syncthreads();
+    // A (*) Num (/) (A W + eps) takes Num's place, and the two arrays change roles
+    for (int e = tid; e < n * k; e += kTinyThreads) {
+      const int i = by_k.div(e), c = e - i * k;
+      float den = 0.0f;
+      for (int b = 0; b < k; ++b) den = fmaf(As[i * kc + b], Ws[b * k + c], den);
+      Num[i * kc + c] = As[i * kc + c] * Num[i * kc + c] / (den + eps);
+    }
+    __syncthreads();
+    float* const old = As;
+    As = Num;
+    Num = old;
   }
-  for (int e = threadIdx.x; e < n * k; e += kTinyThreads) A_int[((int64_t)(e / k) * q + r) * kp + e % k] = As[e];
-  for (int e = threadIdx.x; e < m * kk; e += kTinyThreads) R[(int64_t)r * m * kk + e] = Rs[e];
+  for (int e = tid; e < n * k; e += kTinyThreads) A_int[((int64_t)(e / k) * q + r) * kp + e % k] = As[e / k * kc + e % k];
+  for (int e = tid; e < mkk; e += kTinyThreads) R[(int64_t)r * mkk + e] = Rs[e];
 }
 
-static size_t tiny_fit_lds_bytes(const Dims& d) {
+// with n x k arrays of pitch kc
+static size_t tiny_fit_lds_bytes(const Dims& d, int kc) {
   const size_t n = (size_t)d.n, m = d.m, k = d.k;
-  return (m * n * (n + 1) + 2 * n * k + 2 * m * n * k + 4 * m * k * k + 2 * k * k) * sizeof(float);
+  return (m * n * (n + 1) + 2 * n * kc + 2 * m * n * kc + 4 * m * k * k + 2 * k * k) * sizeof(float);
 }
 
 // everything within 150 KB of LDS
-bool tiny_fit_applies(const Dims& d) { return d.n <= kTinyMaxN && tiny_fit_lds_bytes(d) <= 150 * 1024; }
+bool tiny_fit_applies(const Dims& d) { return d.n <= kTinyMaxN && tiny_fit_lds_bytes(d, d.k) <= 150 * 1024; }
+
+template <int CK>
+static hipError_t launch_tiny_fit_t(const float* X, float* A_int, float* R, const Dims& d, int iters, float eps, uint64_t seed,
+                                    float delta, hipStream_t s) {
+  const size_t lds = tiny_fit_lds_bytes(d, (int)round_up(d.k, CK)) + 12;   // (what follows X starts at 16 bytes)
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute((const void*)tiny_fit_kernel<CK>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  hipLaunchKernelGGL(tiny_fit_kernel<CK>, dim3((unsigned)d.q), dim3(kTinyThreads), lds, s, X, A_int, R, d, iters, eps,
+                     (uint32_t)seed, (uint32_t)(seed >> 32), delta * 0x1p-16f, delta != 0.0f ? 1 : 0);
+  return hipGetLastError();
+}
 
 hipError_t launch_tiny_fit(const float* X, float* A_int, float* R, const Dims& d, int iters, float eps, uint64_t seed,
                            float delta, hipStream_t s) {
   if (!tiny_fit_applies(d)) return hipErrorInvalidValue;
-  const size_t lds = tiny_fit_lds_bytes(d);
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)tiny_fit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  hipLaunchKernelGGL(tiny_fit_kernel, dim3((unsigned)d.q), dim3(kTinyThreads), lds, s, X, A_int, R, d, iters, eps,
-                     (uint32_t)seed, (uint32_t)(seed >> 32), delta * 0x1p-16f, delta != 0.0f ? 1 : 0);
-  return hipGetLastError();
+  // many small slices at ranks 1 and 2 can exceed the LDS with the columns padded to four: one at a time then
+  return tiny_fit_lds_bytes(d, (int)round_up(d.k, 4)) + 12 <= 160 * 1024
+             ? launch_tiny_fit_t<4>(X, A_int, R, d, iters, eps, seed, delta, s)
+             : launch_tiny_fit_t<1>(X, A_int, R, d, iters, eps, seed, delta, s);
 }
 
 }  // namespace nnr
