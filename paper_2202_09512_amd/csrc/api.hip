@@ -123,12 +123,12 @@ nnrescal_status device_error_status(nnrescal_handle* h) {
 }
 
 // ---- building blocks of one iteration -------------------------------------------------------------
-hipError_t compute_G(nnrescal_handle* h) {
+hipError_t compute_G(nnrescal_handle* h, bool cleared) {
   if (h->g_valid) return hipSuccess;
   Prof pf(h, 0);
   const Dims& d = h->d;
   h->g_valid = true;
-  return launch_gram16(h->A, h->A, 0, h->G, 1, d, h->stream, nullptr, h->det_gram, h->det_gram_floats);
+  return launch_gram16(h->A, h->A, 0, h->G, 1, d, h->stream, nullptr, h->det_gram, h->det_gram_floats, cleared);
 }
 
 // S_t = A^T P_t for all m slices
@@ -289,7 +289,8 @@ nnrescal_status mu_step_impl(nnrescal_handle* h, bool with_objective) {
   const bool s_cleared = h->det_gram == nullptr;
   {
     // everything that this iteration's kernels add into, cleared by ONE launch: the denominator core, the objective's
-    // terms, on the dense path the two products of the pass over X, and A^T X_t A
+    // terms, on the dense path the two products of the pass over X, A^T X_t A, and A^T A, whose contents move to where
+    // this iteration reads them (a launch of its own between the R rule and the A rule otherwise: 4.6 us)
     Prof pf(h, 3);
     FillList fl;
     fl.add(h->W, (size_t)d.q * d.k * d.k * sizeof(float));
@@ -299,6 +300,7 @@ nnrescal_status mu_step_impl(nnrescal_handle* h, bool with_objective) {
       fl.add(h->Q, (size_t)d.m * ps * sizeof(float));
     }
     if (s_cleared) fl.add(h->S, (size_t)d.m * d.q * d.k * d.k * sizeof(float));
+    if (!h->det_gram) fl.add(h->G, (size_t)d.q * d.k * d.k * sizeof(float), h->G_now);   // (reproducible mode: overwritten)
     HIPCHK(launch_fill_zero_multi(fl, h->stream));
   }
   if (with_objective) {
@@ -314,7 +316,7 @@ nnrescal_status mu_step_impl(nnrescal_handle* h, bool with_objective) {
   {
     Prof pf(h, 3);
     // with h->obj: <S_t, R_t> and <G R_t G, R_t> of the factors before this update, at no extra pass over X
-    HIPCHK(launch_r_update(h->G, h->S, h->R, h->W, with_objective ? h->obj : nullptr, h->Rp, h->Rq, 0, d.m, d, eps, 1,
+    HIPCHK(launch_r_update(h->det_gram ? h->G : h->G_now, h->S, h->R, h->W, with_objective ? h->obj : nullptr, h->Rp, h->Rq, 0, d.m, d, eps, 1,
                            h->stream, h->det_wpart, h->det_objpart));
   }
   {
@@ -513,7 +515,7 @@ nnrescal_status init_impl(nnrescal_handle** out, const nnrescal_tensor* X, const
       {(void**)&h->R, (size_t)d.q * d.m * kk * sizeof(float)},
       {(void**)&h->G, (size_t)d.q * kk * sizeof(float)},
       {(void**)&h->S, (size_t)d.m * d.q * kk * sizeof(float)},
-      {(void**)&h->W, (size_t)d.q * kk * sizeof(float)},
+      {(void**)&h->W, (size_t)2 * d.q * kk * sizeof(float)},   // and G_now
       {(void**)&h->P, (size_t)d.m * d.n * row * sizeof(float)},
       {(void**)&h->Q, (size_t)d.m * d.n * row * sizeof(float)},
       {(void**)&h->Rp, (size_t)d.q * d.m * d.kp * d.kp * sizeof(float)},
@@ -558,6 +560,7 @@ nnrescal_status init_impl(nnrescal_handle** out, const nnrescal_tensor* X, const
       return fail(nullptr, NNRESCAL_ENOMEM, "the alloc callback returned NULL");
     }
   }
+  h->G_now = h->W + (size_t)d.q * kk;
   auto bail = [&](hipError_t e, const char* what) {
     std::string msg = std::string(what) + ": " + hipGetErrorString(e);
     destroy_impl(h);
@@ -828,7 +831,8 @@ int32_t nnrescal_gather_form(const nnrescal_handle* h) { return h && h->segs_dev
 // address: the address on the current device comes from hipGetSymbolAddress, once per device, and only that pointer
 // is ever handed to kernels.
 // NNRESCAL_STATIC_SCRATCH_BYTES bound what a problem may take, counted with the operand copy of A at 4 bytes per element;
-// its bf16 terms take 8.  The copy is as large as A itself (up to its padding), so at most half of the count (and 16 KB).
+// its bf16 terms take 8, and the place of W holds a copy of G too.  The one is as large as A (up to its padding), the
+// other as G, so that all of it is at most one and a half times the count (and 16 KB).
 constexpr size_t kScratchBytes = (size_t)NNRESCAL_STATIC_SCRATCH_BYTES + NNRESCAL_STATIC_SCRATCH_BYTES / 2 + 65536;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -929,13 +933,18 @@ nnrescal_status nnrescal_mu_step_static(const nnrescal_tensor* X, const nnrescal
   size_t off = 0;
   for (const Req& r : reqs) {
     *r.p = r.bytes ? (void*)(base + off) : nullptr;
-    off += ((r.p == (void**)&h->A_op ? kOperandFloats : 1) * r.bytes + 255) & ~(size_t)255;
+    const size_t times = r.p == (void**)&h->A_op ? kOperandFloats : (r.p == (void**)&h->W ? 2 : 1);   // (W: and G_now)
+    off += (times * r.bytes + 255) & ~(size_t)255;
   }
+  h->G_now = h->W + (size_t)d.q * kk;
   if (off > kScratchBytes) return fail(nullptr, NNRESCAL_EINVAL, "nnrescal_mu_step_static: workspace beyond the static array");
   h->dev_error = status_or_null;       // a device word of the caller's (or none)
   h->dev_error_pinned = false;
-  if (status_or_null) HIPCHK(launch_fill_zero(status_or_null, sizeof(int32_t), h->stream));
-  if (dense) HIPCHK(launch_fill_zero(h->A_op + kOperandFloats * (size_t)d.n_pad * row, kOperandFloats * pad * sizeof(float), h->stream));
+  FillList fl;
+  fl.add(h->G, (size_t)d.q * kk * sizeof(float));
+  fl.add(status_or_null, sizeof(int32_t));
+  if (dense) fl.add(h->A_op + kOperandFloats * (size_t)d.n_pad * row, kOperandFloats * pad * sizeof(float));
+  HIPCHK(launch_fill_zero_multi(fl, h->stream));
   HIPCHK(launch_import_factors(h->A, h->R, A, R, d, h->stream));
   if (!dense) {
     for (int t = 0; t < d.m; ++t) {
@@ -945,6 +954,7 @@ nnrescal_status nnrescal_mu_step_static(const nnrescal_tensor* X, const nnrescal
         HIPCHK(launch_expand_major(X->csc_colptr + (int64_t)t * (d.n + 1), h->csc_major + h->csc_off[t], d.n, nz, h->stream));
     }
   }
+  HIPCHK(compute_G(h, true));
   st = mu_step_impl(h);
   if (st != NNRESCAL_OK) return fail(nullptr, st, h->err);
   HIPCHK(launch_export_factors(A, R, h->A, h->R, h->G, 0, d, h->stream));

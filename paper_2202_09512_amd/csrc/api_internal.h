@@ -55,6 +55,7 @@ struct nnrescal_handle {
   double* det_xnpart = nullptr;   // [kXnormMaxBlocks][q], block sums of ||X||^2
   float* det_side = nullptr;      // sparse: [chunks][2][q kp], pieces of rows that cross chunk borders
   bool xnorm_valid = false;
+  float* G_now = nullptr;  // behind W: A^T A that the running iteration reads while G takes the new A's
   bool g_valid = false;    // G holds A^T A of the current A
   bool aop_valid = false;  // A_op holds the current A (dense path)
   int64_t iterations = 0;
@@ -98,7 +99,7 @@ void destroy_impl(nnrescal_handle* h);
 // EDEVICE if a kernel of this handle has reported a wait that ran out (the factors are then not to be trusted);
 // reliable after a synchronisation of the handle's stream, opportunistic before
 nnrescal_status device_error_status(nnrescal_handle* h);
-hipError_t compute_G(nnrescal_handle* h);
+hipError_t compute_G(nnrescal_handle* h, bool cleared = false);   // cleared: G is zero already
 // the pass over X for the current A: P_t = X^q_t A, Q_t = X^q_t^T A into the handle's P and Q (dense: all slices)
 // only_slice >= 0: that slice alone (its part of P and Q)
 hipError_t dense_pass(nnrescal_handle* h, int only_slice = -1, bool pq_cleared = false);

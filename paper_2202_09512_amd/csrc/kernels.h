@@ -31,9 +31,10 @@ struct FillList {
   static constexpr int kMax = 6;
   void* p[kMax];
   size_t bytes[kMax];                              // multiples of 4
+  void* old[kMax];                                 // where the buffer's contents go first (nullptr: nowhere)
   int count = 0;
-  void add(void* ptr, size_t nbytes) {
-    if (ptr && nbytes && count < kMax) { p[count] = ptr; bytes[count] = nbytes; ++count; }
+  void add(void* ptr, size_t nbytes, void* keep = nullptr) {
+    if (ptr && nbytes && count < kMax) { p[count] = ptr; bytes[count] = nbytes; old[count] = keep; ++count; }
   }
 };
 hipError_t launch_fill_zero_multi(const FillList& fl, hipStream_t s);
@@ -93,7 +94,7 @@ hipError_t launch_gram16(const float* Y, const float* Z, int64_t zstride, float*
                          hipStream_t s, const uint32_t* zmask = nullptr, float* det_part = nullptr,
                          size_t det_part_floats = 0, bool out_cleared = false);
 // The whole A rule over all m slices; also writes the operand-order copy A_op of the new A and G = A^T A of
-// the new A (G is cleared first).  Rp, Rq as written by launch_r_update.  det_part (as for launch_gram16): the new
+// the new A (added to: G has to be zero; reproducible mode: overwritten).  Rp, Rq as written by launch_r_update.  det_part (as for launch_gram16): the new
 // A^T A is then never accumulated inside the rule's kernel but always by a Gram pass with ordered sums.  pmask, qmask (optional, DEVICE,
 // [m][ceil(n / 32)] words): which rows of P_t and Q_t hold anything (the others must be zero and are not read).
 hipError_t launch_a_update16(float* A_int, float* A_op, const float* P, const float* Q, int64_t pq_slice_stride,

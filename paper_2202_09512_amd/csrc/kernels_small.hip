@@ -24,10 +24,14 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 // blockIdx.y: which buffer
 __global__ void fill_zero_multi_kernel(FillList fl) {
   uint32_t* p = (uint32_t*)fl.p[blockIdx.y];
+  uint32_t* old = (uint32_t*)fl.old[blockIdx.y];
   const size_t nwords = fl.bytes[blockIdx.y] / 4;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < nwords; i += stride) p[i] = 0u;
+  for (; i < nwords; i += stride) {
+    if (old) old[i] = p[i];
+    p[i] = 0u;
+  }
 }
 
 hipError_t launch_fill_zero_multi(const FillList& fl, hipStream_t s) {

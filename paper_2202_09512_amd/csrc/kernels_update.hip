@@ -800,9 +800,8 @@ hipError_t launch_a_update16(float* A_int, float* A_op, const float* P, const fl
                              const float* Rp, const float* Rq, const float* W, float* G_out, const Dims& d, float eps,
                              hipStream_t s, const uint32_t* pmask, const uint32_t* qmask, float* det_part,
                              size_t det_part_floats) {
-  // G receives the new A^T A: clear it first (the R rule, which read the old one, has been enqueued before)
-  hipError_t e = launch_fill_zero(G_out, (size_t)d.q * d.k * d.k * sizeof(float), s);
-  if (e != hipSuccess) return e;
+  // G_out receives the new A^T A: added to (it has to be zero), in the reproducible mode overwritten
+  hipError_t e = hipSuccess;
   // reproducible mode: the rule's kernels do not accumulate A^T A (atomic additions); a Gram pass does, in order
   float* G = det_part ? nullptr : G_out;
   const bool gram_pass_always = det_part != nullptr;
@@ -857,7 +856,7 @@ hipError_t launch_a_update16(float* A_int, float* A_op, const float* P, const fl
   if (e != hipSuccess) return e;
   if (fused_g && !gram_pass_always) return hipSuccess;
   // wide ranks (and the reproducible mode): the Gram pass is a launch of its own
-  return launch_gram16(A_int, A_int, 0, G_out, 1, d, s, nullptr, det_part, det_part_floats);
+  return launch_gram16(A_int, A_int, 0, G_out, 1, d, s, nullptr, det_part, det_part_floats, true);
 }
 
 }  // namespace nnr
