@@ -290,10 +290,13 @@ hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
   const int w = g.wa > g.wb ? g.wa : g.wb;
   const int TW = w <= 16 ? 16 : (w <= 32 ? 32 : 64);
   const int tiles = (int)(ceil_div(g.wa, TW) * ceil_div(g.wb, TW));
-  // enough blocks to fill the chip, but at least 512 rows each to keep the atomic traffic small
+  // enough blocks to fill the chip, but at least 512 rows each to keep the atomic traffic small; where that leaves compute
+  // units idle a block's chain of 64-row steps (10 us each, loads not overlapped) is the time: one step per block then
+  // (the sweep of ranks 2 ... 6 on 500 entities, 6 slices, 8 members: 11.6 -> 10.8 ms)
   const int64_t want_split = ceil_div(2048, (int64_t)tiles * nbatch);
+  const int64_t least = (int64_t)tiles * nbatch * ceil_div(g.n, 512) < 256 ? 64 : 512;
   int64_t rows_per_block = round_up(ceil_div(g.n, want_split), 64);
-  if (rows_per_block < 512) rows_per_block = 512;
+  if (rows_per_block < least) rows_per_block = least;
   const int nsplit = (int)ceil_div(g.n, rows_per_block);
   dim3 grid((unsigned)ceil_div(g.wa, TW), (unsigned)ceil_div(g.wb, TW), (unsigned)(nbatch * nsplit));
   if (TW == 16)
