@@ -36,6 +36,7 @@
 // waits for each other), a wave that generates beside one that multiplies (7.1 ms), 16 waves per workgroup with half the
 // registers each (6.6 ... 6.9 ms).
 #include "bf16split.h"
+#include "dense_reads.h"
 #include "kernels.h"
 
 namespace nnr {
@@ -83,10 +84,9 @@ hipError_t launch_pack_operand(const float* A_int, float* A_op, const Dims& d, h
   return hipGetLastError();
 }
 
-// The "row" orientation of one 16 x 16 tile: lane (l16, row) holds X[i0 + l16][j0 + 4*row + r], r = 0..3.  It is ONE
-// 16-byte buffer load per lane on every path (rows need no more than the 4-byte alignment of a float; what lies beyond
-// the tensor's end reads as zero), so that the number of loads in flight is known wherever one of them is waited for.
-// take_tile puts zeros in the places of other rows and columns.
+// A tile of X in "row" orientation is ONE 16-byte buffer load per lane on every path (dense_reads.h: rows need no more
+// than the 4-byte alignment of a float, what lies beyond the tensor's end reads as zero), so that the number of loads in
+// flight is known wherever one of them is waited for.  take_tile puts zeros in the places of other rows and columns.
 __device__ __forceinline__ floatx4 take_tile(floatx4 x, int rows_left, int cols_left) {
   // rows_left, cols_left: elements of the matrix from this lane's first one on
   const bool in = rows_left > 0;
@@ -188,7 +188,6 @@ __global__ void __launch_bounds__(W * 64, 2)
   const bool ordered = Ppart != nullptr;
   float* Pt = ordered ? Ppart + (int64_t)panel * ppart_stride + (int64_t)t * out_tstride : P + (int64_t)t * out_tstride;
   float* Qt = Q + (int64_t)t * out_tstride;
-  const int n32 = (int)n;
   int tiles = (int)((n - jp0 + 15) >> 4);           // tiles of the panel that hold columns of the matrix
   if (tiles > W) tiles = W;
   const int cols = (int)(n - jp0 < 16 * W ? n - jp0 : 16 * W);   // columns of the panel
@@ -222,13 +221,12 @@ __global__ void __launch_bounds__(W * 64, 2)
   // X tile of a strip (first row i0) and a tile column; the loads run two steps ahead, across strip boundaries.  A
   // tile beyond the matrix, or rows beyond the chunk: whatever is there is loaded and never used.
   const int64_t total = (int64_t)m * n * n;
-  const uint32_t x_lane = (uint32_t)(l16 * n32 + 4 * row) * 4u;
+  const uint32_t x_lane = tile_lane_offset((uint32_t)n, l16, row);
   auto x_fetch = [&](int64_t i0, int jt) -> floatx4 {
-    const int64_t first = (t * n + i0) * n + jp0;   // wave-uniform
-    const int64_t bytes = 4 * (total - first);
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(X + first), 0, (int)(uint32_t)(bytes < 0xFFFFFFFFLL ? bytes : 0xFFFFFFFFLL), 0x00020000);
-    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)x_lane, 64 * jt, 0));
+    const TileBuffer b = tile_buffer(n, total, t, i0, jp0);   // wave-uniform
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + b.first), 0, (int)b.bytes, 0x00020000);
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)tile_voffset(x_lane, jt), 0, 0));
   };
   uintx8 bP[NG], bq[NG];
   auto bp_fetch = [&](int jt) {
