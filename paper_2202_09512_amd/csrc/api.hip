@@ -127,8 +127,9 @@ hipError_t compute_G(nnrescal_handle* h, bool cleared) {
   if (h->g_valid) return hipSuccess;
   Prof pf(h, 0);
   const Dims& d = h->d;
-  h->g_valid = true;
-  return launch_gram16(h->A, h->A, 0, h->G, 1, d, h->stream, nullptr, h->det_gram, h->det_gram_floats, cleared);
+  const hipError_t e = launch_gram16(h->A, h->A, 0, h->G, 1, d, h->stream, nullptr, h->det_gram, h->det_gram_floats, cleared);
+  h->g_valid = e == hipSuccess;
+  return e;
 }
 
 // S_t = A^T P_t for all m slices
@@ -302,6 +303,7 @@ nnrescal_status mu_step_impl(nnrescal_handle* h, bool with_objective) {
     if (s_cleared) fl.add(h->S, (size_t)d.m * d.q * d.k * d.k * sizeof(float));
     if (!h->det_gram) fl.add(h->G, (size_t)d.q * d.k * d.k * sizeof(float), h->G_now);   // (reproducible mode: overwritten)
     HIPCHK(launch_fill_zero_multi(fl, h->stream));
+    h->g_valid = false;                            // until the A rule has been enqueued: an error in between leaves G cleared
   }
   if (with_objective) {
     nnrescal_status st = xnorm_enqueue(h);
@@ -321,10 +323,11 @@ nnrescal_status mu_step_impl(nnrescal_handle* h, bool with_objective) {
   }
   {
     Prof pf(h, 5);
-    // writes the new A (dense path: in both layouts) and its A^T A: G (and A_op) stay valid
+    // writes the new A (dense path: in both layouts) and its A^T A: G is valid again, A_op stays so
     HIPCHK(launch_a_update16(h->A, h->A_op, h->P, h->Q, ps, h->Rp, h->Rq, h->W, h->G, d, eps, h->stream,
                              h->use_masks ? h->pmask : nullptr, h->use_masks ? h->qmask : nullptr, h->det_gram,
                              h->det_gram_floats));
+    h->g_valid = true;
   }
   h->iterations += 1;
   return NNRESCAL_OK;
