@@ -33,10 +33,14 @@ struct FillList {
   size_t bytes[kMax];                              // multiples of 4
   void* old[kMax];                                 // where the buffer's contents go first (nullptr: nowhere)
   int count = 0;
+  bool overflow = false;                           // a buffer had no place: the launch is refused
   void add(void* ptr, size_t nbytes, void* keep = nullptr) {
-    if (ptr && nbytes && count < kMax) { p[count] = ptr; bytes[count] = nbytes; old[count] = keep; ++count; }
+    if (!ptr || !nbytes) return;
+    if (count == kMax) { overflow = true; return; }
+    p[count] = ptr; bytes[count] = nbytes; old[count] = keep; ++count;
   }
 };
+// hipErrorInvalidValue, and nothing launched, for a list that has lost a buffer
 hipError_t launch_fill_zero_multi(const FillList& fl, hipStream_t s);
 // Fixed-order sums of partial results (the reproducible mode: partial sums are stored, not added atomically, and
 // summed here in the order of their index): out[e] = (accumulate ? out[e] : 0) + parts[0][e] + parts[1][e] + ...,

@@ -35,6 +35,7 @@ __global__ void fill_zero_multi_kernel(FillList fl) {
 }
 
 hipError_t launch_fill_zero_multi(const FillList& fl, hipStream_t s) {
+  if (fl.overflow) return hipErrorInvalidValue;
   if (fl.count == 0) return hipSuccess;
   size_t most = 0;
   for (int i = 0; i < fl.count; ++i) most = fl.bytes[i] > most ? fl.bytes[i] : most;

@@ -140,3 +140,36 @@ def program(tmp_path_factory):
 def test_gram_is_formed_again_after_a_failed_launch(program, k, reproducible):
     out = subprocess.run([program, str(k), str(reproducible)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stdout + out.stderr
+
+
+FILL_SOURCE = r"""
+#include "kernels.h"
+#include <cstdio>
+using namespace nnr;
+int main() {
+  int32_t word[FillList::kMax + 1] = {};
+  FillList fl;
+  for (int i = 0; i < FillList::kMax; ++i) fl.add(word + i, 4);
+  fl.add(nullptr, 4);                              // no buffer: needs no place
+  fl.add(word, 0);
+  const bool whole = fl.count == FillList::kMax && !fl.overflow;
+  fl.add(word + FillList::kMax, 4);
+  const hipError_t e = launch_fill_zero_multi(fl, nullptr);
+  printf("whole %d, one too many: %d\n", (int)whole, (int)e);
+  return whole && e == hipErrorInvalidValue ? 0 : 1;
+}
+"""
+
+
+def test_fill_list_refuses_what_it_cannot_hold(tmp_path):
+    """A buffer that does not fit the list must not be left uncleared without a word."""
+    from paper_2202_09512_amd import build
+    obj = os.path.join(build.HERE, "_build", "kernels_small.o")
+    if not os.path.exists(obj):
+        build.build(verbose=False)
+    src, exe = tmp_path / "fill.cpp", tmp_path / "fill"
+    src.write_text(FILL_SOURCE)
+    subprocess.run(["/opt/rocm/bin/hipcc", "-std=c++17", "-O1", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(build.HERE, "csrc"),
+                    str(src), "-x", "none", obj, "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stdout + out.stderr
