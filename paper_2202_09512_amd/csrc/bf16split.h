@@ -1,9 +1,14 @@
 // fp32 operands of the matrix products as sums of three bf16 terms.  v_mfma_f32_16x16x32_bf16 does eight times the
-// work of v_mfma_f32_16x16x4_f32 in about half its cycles, so a product x y kept as the six term products of order
-// 2^-16 and larger, accumulated in fp32, costs a third of the fp32 instructions' cycles, and vector instructions of the
-// other wave run beside it, which they do not beside fp32 MFMA (measured on this GPU).
-//   y = y1 + y2 + y3, every term the rest of the ones before it rounded to 8 bits: the sum is y to 2^-26 |y|.
-// bf16 has fp32's exponent range, so that nothing is scaled; a head that would round up to infinity is cut instead.
+// work of v_mfma_f32_16x16x4_f32 in about half its cycles, so a product x y kept as six term products, accumulated in
+// fp32, costs a third of the fp32 instructions' cycles, and vector instructions of the other wave run beside it, which
+// they do not beside fp32 MFMA (measured on this GPU).
+//   x = x1 + d1 + d2 and y = y1 + y2 + y3, both exactly: 24 bits in three terms of 8.  Terms below 2^-133 are lost, so
+//   values below 2^-110 have fewer bits than in fp32.
+//   Of x y, d1 y3 and d2 y2 are left out (and d2 y3): below 2^-23 of it each.  One product is off by at most 2^-22.2, 2^-24.8
+//   in the root mean square (measured; an fp32 product, which is only rounded once: 2^-24, 2^-25.2), random in sign; sums
+//   of thousands of products are as good as those of the fp32 instructions (see kernels_dense.hip).
+// bf16 has fp32's exponent range, so that nothing is scaled; a head that would round up to infinity is cut instead.  An
+// infinite operand gives NaN (its rest is infinity minus infinity).
 #pragma once
 #include "common.h"
 
@@ -29,11 +34,22 @@ __device__ __forceinline__ uint32_t pack_round(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
 }
 
-// v = hi + lo + rest of 2^-18 |v|, hi and lo rounded to bf16, for four values of a lane (two packed words each)
+// v = hi + lo + rest of 2^-16 |v|, hi and lo rounded to bf16, for four values of a lane (two packed words each)
 __device__ __forceinline__ void split2(const float (&v)[4], uintx2& hi, uintx2& lo) {
   hi = uintx2{pack_round(v[0], v[1]), pack_round(v[2], v[3])};
   lo = uintx2{pack_round(v[0] - __uint_as_float(hi.x << 16), v[1] - __uint_as_float(hi.x & 0xFFFF0000u)),
               pack_round(v[2] - __uint_as_float(hi.y << 16), v[3] - __uint_as_float(hi.y & 0xFFFF0000u))};
+}
+
+// v = x1 + d1 + d2, exactly: the head x1 is v cut to 8 bits, d1 the rest of 16 bits rounded to 8, and what is left then has 8
+__device__ __forceinline__ void split3(const float (&v)[4], uintx2& x1, uintx2& d1, uintx2& d2) {
+  x1 = uintx2{pack_cut(v[0], v[1]), pack_cut(v[2], v[3])};
+  float r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = v[i] - cut_to_bf16(v[i]);
+  d1 = uintx2{pack_round(r[0], r[1]), pack_round(r[2], r[3])};
+  d2 = uintx2{pack_cut(r[0] - __uint_as_float(d1.x << 16), r[1] - __uint_as_float(d1.x & 0xFFFF0000u)),
+              pack_cut(r[2] - __uint_as_float(d1.y << 16), r[3] - __uint_as_float(d1.y & 0xFFFF0000u))};
 }
 
 // The four values that a lane supplies to one 16-deep product, as right operands of depth-32 instructions, which take

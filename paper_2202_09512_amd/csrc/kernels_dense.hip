@@ -3,8 +3,8 @@
 // with X^r = X (*) Delta^r generated on the fly (Alg. 4) from a counter-based random stream, so the
 // perturbed tensors are never stored and X is read once for all members of a group.
 //
-// Mapping to CDNA4.  The contraction runs on the bf16 matrix cores at fp32 precision: every operand is a sum of three
-// bf16 terms and a 16 x 16 x 16 product of fp32 numbers is three v_mfma_f32_16x16x32_bf16 (bf16split.h).  They take 50
+// Mapping to CDNA4.  The contraction runs on the bf16 matrix cores: every fp32 operand is a sum of three bf16 terms, without
+// a rest, and a 16 x 16 x 16 product of fp32 numbers is three v_mfma_f32_16x16x32_bf16 (bf16split.h).  They take 50
 // cycles; the four v_mfma_f32_16x16x4_f32 of the same product take 129 and, sharing the vector ALUs, let no vector
 // instruction run beside them, while the generator's multiplications run beside bf16 MFMA for free (measured).
 // Of an instruction's result D[16x16], lane l holds D[4*(l/16)+r][l%16] in register r.  The perturbed X tile is the left
@@ -30,11 +30,12 @@
 //
 // What bounds it: the vector instructions of a tile (generator, splitting, conversions), with two waves per SIMD at 256
 // registers each; the additions of P to memory cost another 17 % (measured by leaving them out).  Against the kernel with
-// fp32 MFMA, one launch for all slices: n = 16384, 4 slices, 8 members, rank 16: 7.02 -> 6.48 ms; n = 2160, 20 slices, 8
-// members, rank 24: 1337 -> 1113 us; n = 2048, 8 slices, 6 members, rank 64: 670 -> 512 us.
-// Measured and left out: one Philox block shared by a pair of waves through LDS (6.8 ... 7.2 ms at n = 16384: the pair
-// waits for each other), a wave that generates beside one that multiplies (7.1 ms), 16 waves per workgroup with half the
-// registers each (6.6 ... 6.9 ms).
+// fp32 MFMA, one launch for all slices, any delta > 0: n = 16384, 4 slices, 8 members, rank 16: 7.05 -> 6.40 ms; n = 2160,
+// 20 slices, 8 members, rank 24: 1342 -> 1127 us; n = 2048, 8 slices, 6 members, rank 64: 674 -> 511 us.
+// Measured and left out: a head x1 = that of X, common to the members, with each member's distance from it in two terms
+// (6.13 ms at n = 16384, but a product was off by up to 2^-20.3 at delta = 0.03 and 2^-19.3 at 1/16); one Philox block shared
+// by a pair of waves through LDS (6.8 ... 7.2 ms: the pair waits for each other), a wave that generates beside one that
+// multiplies (7.1 ms), 16 waves per workgroup with half the registers each (6.6 ... 6.9 ms); these three with the common head.
 #include "bf16split.h"
 #include "dense_reads.h"
 #include "kernels.h"
@@ -110,26 +111,23 @@ __device__ __forceinline__ u32x4 front_halves(u32x4 w, int hoff) {
   return w;
 }
 
-// How a member's perturbed element is split into bf16 terms (left operand x1 + d1 + d2 of both products):
-//   kPlain       delta = 0: the three terms of X itself, one split for all members;
-//   kSharedHead  delta <= kSharedHeadMaxDelta: x1 is the head of X, common to the members of a group; d1 + d2 is the
-//                member's distance from it, at most (delta + 2^-7) X, which two terms hold to 2^-18 of that;
-//   kOwnHead     larger delta: every member has a head of its own.
-enum { kPlain = 0, kSharedHead = 1, kOwnHead = 2 };
-
 // Dynamic LDS layout (floats):
 //   [0, W*NG*256)          panel-wide Q accumulator in MFMA accumulator order: qlds[tile][group][lane][4]
-//   then per wave               transposition tiles of bf16 terms: 64 pieces of 8 bytes per
-//                               term, d1 and d2 of every member, then the head(s) x1
+//   then per wave          transposition tiles of bf16 terms: 64 pieces of 8 bytes per term, d1 and d2 of every member
+//                          (of X itself where nothing is perturbed), then the heads x1
 //   then W ints            completed steps per wave
-template <int NT, int QB, int MODE, int W>
+// With 8 members and 8 waves all of it is 32 bytes more than the 160 KB of a compute unit: the last member's head then
+// has no place of its own and takes the first one's, once that has been read back.
+template <int NT, int QB, bool PERTURB, int W>
 struct StreamShape {
   static constexpr int NG = QB * NT;                            // product groups (member, 16-column block)
-  static constexpr int NREST = MODE == kPlain ? 1 : QB;         // rests (d1, d2) per element
-  static constexpr int NHEAD = MODE == kOwnHead ? QB : 1;       // heads (x1) per element
-  static constexpr int QLDS = W * NG * 256;                    // floats of the Q accumulator
-  static constexpr int TBUF = NREST * 256 + NHEAD * 128;        // floats of transposition space per wave
-  static constexpr size_t bytes = (size_t)(QLDS + W * TBUF + W) * sizeof(float);
+  static constexpr int NSPLIT = PERTURB ? QB : 1;               // values per element that are split into terms
+  static constexpr int QLDS = W * NG * 256;                     // floats of the Q accumulator
+  static constexpr int lds_floats(int heads) { return QLDS + W * (NSPLIT * 256 + heads * 128) + W; }
+  static constexpr bool LATE = lds_floats(NSPLIT) * (int)sizeof(float) > 160 * 1024;
+  static constexpr int NHEAD = LATE ? NSPLIT - 1 : NSPLIT;      // places for heads
+  static constexpr int TBUF = NSPLIT * 256 + NHEAD * 128;       // floats of transposition space per wave
+  static constexpr size_t bytes = (size_t)lds_floats(NHEAD) * sizeof(float);
 };
 
 // four 16-bit values of one column of a row-major LDS tile (the 16 lanes of a group each address four of a row)
@@ -139,7 +137,7 @@ __device__ __forceinline__ uintx2 read_transposed(const void* lds_ptr) {
                                         (__attribute__((address_space(3))) s4*)(__attribute__((address_space(3))) void*)lds_ptr));
 }
 
-template <int NT, int QB, int MODE, int W>
+template <int NT, int QB, bool PERTURB, int W>
 __global__ void __launch_bounds__(W * 64, 2)
     dense_stream_kernel(const float* __restrict__ X, const uintx4* __restrict__ A_op, float* __restrict__ P,
                         float* __restrict__ Q, int64_t n, int m, int q, int k, int qfirst, int ngroups, int n_chunks,
@@ -147,8 +145,8 @@ __global__ void __launch_bounds__(W * 64, 2)
                         const uintx4* __restrict__ A_opQ, int64_t aop_tstride, int64_t out_tstride,
                         int32_t* __restrict__ timeout_flag, int spin_limit, float* __restrict__ Ppart,
                         int64_t ppart_stride) {
-  typedef StreamShape<NT, QB, MODE, W> Shape;
-  constexpr int NG = Shape::NG, NREST = Shape::NREST, NHEAD = Shape::NHEAD;
+  typedef StreamShape<NT, QB, PERTURB, W> Shape;
+  constexpr int NG = Shape::NG, NSPLIT = Shape::NSPLIT;
   extern __shared__ __attribute__((aligned(16))) float lds[];
   float* qlds = lds;
 
@@ -276,8 +274,8 @@ __global__ void __launch_bounds__(W * 64, 2)
   const int get = 4 * (4 * row + (l16 >> 2)) + ((l16 & 3) ^ row);
   char* const rest_put = tbuf + 8 * put;
   char* const rest_get = tbuf + 8 * get;
-  char* const head_put = tbuf + NREST * 1024 + 8 * put;
-  char* const head_get = tbuf + NREST * 1024 + 8 * get;
+  char* const head_put = tbuf + NSPLIT * 1024 + 8 * put;
+  char* const head_get = tbuf + NSPLIT * 1024 + 8 * get;
   const float pa = 2.0f * dscaled, pc = __fmaf_rn(-65535.0f, dscaled, 1.0f);   // as in perturbed()
 
   for (int rnd = 0; rnd < nrounds; ++rnd) {
@@ -294,6 +292,7 @@ __global__ void __launch_bounds__(W * 64, 2)
       const int jt = tile_of(s);
       const bool work = have_strip && jt < tiles;   // wave-uniform
       floatx4 xc = x;
+      uintx2 late_head = {0u, 0u};                  // the last member's head where it has no place in LDS yet
       x = x_fetch(s + 2 < W ? i0 : i0_next, tile_of(s + 2));
       if (work) {
         if (rows_left < 16 || 16 * jt + 16 > cols) {          // wave-uniform
@@ -303,7 +302,7 @@ __global__ void __launch_bounds__(W * 64, 2)
         // ---- the generator: one Philox block per element serves all QB members
         __builtin_amdgcn_s_setprio(kPrioGenerator);
         u32x4 w[4];
-        if (MODE != kPlain) {
+        if (PERTURB) {
           const uint64_t e0 = (uint64_t)(i0 + l16) * (uint64_t)n + (uint64_t)(jp0 + 16 * jt + 4 * row);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -315,17 +314,16 @@ __global__ void __launch_bounds__(W * 64, 2)
         // ---- per member: the terms of the perturbed tile in "row" orientation -> P products; park them in LDS for
         //      the transpose
         __builtin_amdgcn_s_setprio(kPrioPProducts);
-        float xa[4], rc[4];                         // the rest of a member's element over the head: xa * half + rc
-        uintx2 x1 = {pack_cut(xcur[0], xcur[1]), pack_cut(xcur[2], xcur[3])};
-        uintx2 d1, d2;
+        float xa[4], xc1[4];                        // a member's element: xa * half + xc1, as in perturbed()
+        uintx2 x1, d1, d2;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           xa[r] = __fmul_rn(xcur[r], pa);
-          rc[r] = (MODE == kPlain ? xcur[r] : __fmul_rn(xcur[r], pc)) - (MODE == kOwnHead ? 0.0f : cut_to_bf16(xcur[r]));
+          xc1[r] = __fmul_rn(xcur[r], pc);
         }
-        if (MODE != kOwnHead) *reinterpret_cast<uintx2*>(head_put) = x1;
-        if (MODE == kPlain) {
-          split2(rc, d1, d2);
+        if (!PERTURB) {
+          split3(xcur, x1, d1, d2);
+          *reinterpret_cast<uintx2*>(head_put) = x1;
           *reinterpret_cast<uintx2*>(rest_put) = d1;
           *reinterpret_cast<uintx2*>(rest_put + 512) = d2;
         }
@@ -336,20 +334,16 @@ __global__ void __launch_bounds__(W * 64, 2)
 #pragma unroll
           for (int u = 0; u < PB; ++u) {
             const int qq = q2 + u;
-            if (MODE != kPlain) {
-              float d[4];
+            if (PERTURB) {
+              float v[4];
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
                 const uint32_t word = (qq >> 1) == 0 ? w[r].x : (qq >> 1) == 1 ? w[r].y : (qq >> 1) == 2 ? w[r].z : w[r].w;
-                d[r] = __fmaf_rn(xa[r], (qq & 1) ? (float)(word >> 16) : (float)(word & 0xFFFFu), rc[r]);
+                v[r] = __fmaf_rn(xa[r], (qq & 1) ? (float)(word >> 16) : (float)(word & 0xFFFFu), xc1[r]);
               }
-              if (MODE == kOwnHead) {               // d is the perturbed value itself
-                x1 = uintx2{pack_cut(d[0], d[1]), pack_cut(d[2], d[3])};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) d[r] -= cut_to_bf16(d[r]);
-                *reinterpret_cast<uintx2*>(head_put + 512 * qq) = x1;
-              }
-              split2(d, d1, d2);
+              split3(v, x1, d1, d2);
+              if (qq < Shape::NHEAD) *reinterpret_cast<uintx2*>(head_put + 512 * qq) = x1;
+              else late_head = x1;
               *reinterpret_cast<uintx2*>(rest_put + 1024 * qq) = d1;
               *reinterpret_cast<uintx2*>(rest_put + 1024 * qq + 512) = d2;
             }
@@ -381,23 +375,26 @@ __global__ void __launch_bounds__(W * 64, 2)
         const bool mine = wait_for_neighbour(rnd * W + s);   // wave-uniform
         float4* qt = reinterpret_cast<float4*>(qlds) + (jt * NG) * 64 + lane;
         // QH members at a time: all LDS reads first (one wait), then the products back to back, then the stores (with all
-        // 8 groups at a time the registers run out; halves spill 8 and are 2 % slower than quarters at n = 16384)
+        // 8 groups at a time, or half of them, the registers run out)
         constexpr int QH = NG < 8 || QB == 1 ? QB : (QB > 2 ? QB / 4 : 1);
-        uintx2 x1t[NHEAD];
-        if (MODE != kOwnHead) x1t[0] = read_transposed(head_get);
 #pragma unroll
         for (int q1 = 0; q1 < QB; q1 += QH) {
-          uintx2 d1t[QH], d2t[QH];
+          uintx2 x1t[QH], d1t[QH], d2t[QH];
           floatx4 qa[QH * NT];
           float4 c[QH * NT];
 #pragma unroll
           for (int h = 0; h < QH; ++h) {
-            if (MODE == kOwnHead) x1t[q1 + h] = read_transposed(head_get + 512 * (q1 + h));
-            if (NREST > 1 || h == 0) {
-              const int at = NREST > 1 ? 1024 * (q1 + h) : 0;
-              d1t[h] = read_transposed(rest_get + at);
-              d2t[h] = read_transposed(rest_get + at + 512);
-            }
+            const int v = NSPLIT > 1 ? q1 + h : 0;   // (nothing perturbed: the terms of X serve every member)
+            x1t[h] = read_transposed(head_get + 512 * (v < Shape::NHEAD ? v : 0));
+            d1t[h] = read_transposed(rest_get + 1024 * v);
+            d2t[h] = read_transposed(rest_get + 1024 * v + 512);
+          }
+          if (Shape::LATE && q1 == 0) {             // (a wave's LDS accesses are carried out in order)
+            static_assert(!Shape::LATE || QH < QB, "the first head has been read before the last one takes its place");
+            *reinterpret_cast<uintx2*>(head_put) = late_head;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
           }
 #pragma unroll
           for (int g = 0; g < QH * NT; ++g) {
@@ -410,8 +407,7 @@ __global__ void __launch_bounds__(W * 64, 2)
 #pragma unroll
             for (int g = 0; g < QH * NT; ++g) {
               const int h = g / NT;
-              qa[g] = mfma_terms(i, x1t[NHEAD == 1 ? 0 : q1 + h], d1t[NREST == 1 ? 0 : h], d2t[NREST == 1 ? 0 : h],
-                                 bq[q1 * NT + g], qa[g]);
+              qa[g] = mfma_terms(i, x1t[h], d1t[h], d2t[h], bq[q1 * NT + g], qa[g]);
             }
           __builtin_amdgcn_sched_barrier(0);
           if (mine) {
@@ -477,7 +473,7 @@ __global__ void __launch_bounds__(W * 64, 2)
 
 const char* dense_stream_kernel_name() { return "dense_stream_kernel"; }
 
-template <int NT, int QB, int MODE, int W>
+template <int NT, int QB, bool PERTURB, int W>
 static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qfirst,
                                   int ngroups, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   const int t_first = o.t_first;
@@ -489,11 +485,11 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
   const int64_t ppart_stride = (int64_t)d.m * d.n * d.q * d.kp;   // one copy of P per panel
   if (Ppart && out_tstride != d.n * d.q * (int64_t)d.kp) return hipErrorInvalidValue;   // (not with summed slices)
   static_assert(QB * NT <= 8, "at most 8 product groups per tile");
-  constexpr size_t lds = StreamShape<NT, QB, MODE, W>::bytes;
+  constexpr size_t lds = StreamShape<NT, QB, PERTURB, W>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, MODE, W>,
+    hipError_t e = hipFuncSetAttribute((const void*)dense_stream_kernel<NT, QB, PERTURB, W>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done = true;
@@ -521,18 +517,11 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
   n_chunks = ceil_div(d.n, rows_per_chunk);
   const int64_t total = n_panels * n_chunks * d.m * ngroups;
   if (total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_stream_kernel<NT, QB, MODE, W>), dim3((unsigned)total), dim3(W * 64), lds, s, X,
+  hipLaunchKernelGGL((dense_stream_kernel<NT, QB, PERTURB, W>), dim3((unsigned)total), dim3(W * 64), lds, s, X,
                      (const uintx4*)A_op, P, Q, d.n, d.m, d.q, d.k, qfirst, ngroups, (int)n_chunks, rows_per_chunk,
                      (uint32_t)seed, (uint32_t)(seed >> 32), delta * 0x1p-16f, t_first, (const uintx4*)A_opQ,
                      o.aop_tstride / 4, out_tstride, timeout_flag, spin_limit, Ppart, ppart_stride);
   return hipGetLastError();
-}
-
-// Up to this delta the members' elements share the head of X's (see kSharedHead): the products that are left out
-// (terms of order delta 2^-18 of the result) are then below 2^-22 of it, random in sign, under the rounding of fp32 sums.
-constexpr float kSharedHeadMaxDelta = 0.0625f;
-static int split_mode(float delta) {
-  return delta == 0.0f ? kPlain : (delta <= kSharedHeadMaxDelta ? kSharedHead : kOwnHead);
 }
 
 // Members per group so that (members) x (16-column blocks) <= 8 product groups: 8 members for k <= 16,
@@ -579,12 +568,8 @@ template <int NT, int QB, int W>
 static hipError_t launch_stream_qb(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int ngroups,
                                    uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   if constexpr (QB * NT <= 8 && (W == kWaves || QB * NT <= (NT > 2 ? NT : 2))) {
-    switch (split_mode(delta)) {
-      case kPlain: return launch_stream_t<NT, QB, kPlain, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
-      case kSharedHead: return launch_stream_t<NT, QB, kSharedHead, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
-      default:
-        if constexpr (QB <= 4) return launch_stream_t<NT, QB, kOwnHead, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
-    }
+    return delta == 0.0f ? launch_stream_t<NT, QB, false, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o)
+                         : launch_stream_t<NT, QB, true, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
   }
   return hipErrorInvalidValue;
 }
@@ -596,7 +581,6 @@ static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, 
                                    uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
   const StreamForm f = stream_form(d);
   int qb = f.members;
-  if (split_mode(delta) == kOwnHead && qb > 4) qb = 4;   // (8 members' transposition tiles with their heads exceed the LDS)
   if (f.merged) count = (int)round_up(count, qb);
   if (f.waves == 4 && !o.Ppart) {                   // (the reproducible mode's copies of P are one per 128 columns)
     return qb == 1 ? launch_stream_qb<NT, 1, 4>(X, A_op, P, Q, d, qf, count, seed, delta, s, o)

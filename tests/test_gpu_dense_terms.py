@@ -1,10 +1,16 @@
 """The dense pass over X keeps its fp32 operands as sums of three bf16 terms.  Both products of a slice against 64-bit
 products of the explicitly perturbed tensor (`nnrescal_perturb`, which the parity tests hold to the oracle bit for bit),
-member by member and column by column, at the edges of its tiles and panels (narrow and wide), for every way the elements
-are split (delta = 0, up to 1/16, above), with factors of both signs and columns and tensors of very different size.
+member by member and column by column, at the edges of its tiles and panels (narrow and wide), for delta = 0, small and
+large, with factors of both signs and columns and tensors of very different size.
 
-Bar per member and column, relative to the column's norm: the terms carry an operand to 2^-25 and the term products
-that are left out are below 2^-20 of a product, random in sign; the fp32 sums of n terms add about sqrt(n) 2^-24."""
+Bar per member and column of sums, relative to the column's norm: single products are within 2^-21.4 (below), random in
+sign; the fp32 sums of n terms add about sqrt(n) 2^-24.  That bar grows with n while the errors of the terms average out,
+so a lost low-order term is looked for where every result is ONE product: X with one entry per row and column.
+
+Bar per product: its operands are held exactly; the two term products that are left out are below 2^-23 each, and three
+accumulating instructions and a final sum may cut a unit of 2^-24 each: 1.5 * 2^-22.  The root mean square over thousands
+of products is 2^-24.8 by measurement (2^-25.2 is the rounding of the result alone); with 2^-24.5 as a bar, an operand
+held to 2^-22 instead of 2^-24 fails, and so does any lost term (2^-17 or more)."""
 import numpy as np
 import pytest
 import torch
@@ -62,3 +68,41 @@ def test_products_range_and_signs(lib, xscale):
 @pytest.mark.parametrize("delta", [0.0, 0.03, 0.5])
 def test_products_in_every_form(lib, n, m, k, q, delta):
     _check(lib, n, m, k, q, delta)
+
+
+def _check_single_products(lib, n, k, q, delta, deterministic=False, signs=False):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + 7 * k + q)
+    X = torch.zeros((1, n, n), device=DEV)
+    rows, pi = torch.arange(n, device=DEV), torch.randperm(n, generator=g, device=DEV)
+    X[0, rows, pi] = 1.0 + torch.rand(n, generator=g, device=DEV)
+    A = 1.0 + torch.rand((q, n, k), generator=g, device=DEV)
+    if signs:
+        A = A * torch.where(torch.rand((q, n, k), generator=g, device=DEV) < 0.5, -1.0, 1.0)
+    R = torch.ones((q, 1, k, k), device=DEV)
+    h = lib.nnrescal_init(lib.DenseX(X), k=k, q=q, delta=delta, seed=n, A0=A, R0=R, deterministic=deterministic)
+    P, Q = lib.nnrescal_products(h, 0)
+    lib.nnrescal_destroy(h)
+    errs = []
+    for r in range(q):
+        x = (lib.nnrescal_perturb(lib.DenseX(X), r, delta, n)[0] if delta > 0 else X[0])[rows, pi].double()[:, None]
+        a = A[r].double()
+        want_p, want_q = x * a[pi], torch.empty_like(a)
+        want_q[pi] = x * a
+        errs.append(torch.stack([((P[r].double() - want_p) / want_p).abs(), ((Q[r].double() - want_q) / want_q).abs()]))
+    err = torch.stack(errs)
+    for which in (0, 1):
+        worst, rms = err[:, which].max().item(), err[:, which].square().mean().sqrt().item()
+        assert worst <= 1.5 * 2.0 ** -22 and (rms <= 2.0 ** -24.5 or n * q * k < 1000), (n, k, q, delta, "PQ"[which], worst, rms)
+
+
+@pytest.mark.parametrize("n,k,q", [(17, 3, 1), (130, 8, 4), (333, 8, 10), (1000, 16, 15), (2176, 16, 8), (2176, 32, 4), (640, 64, 3),
+                                   (4200, 16, 13)])
+@pytest.mark.parametrize("delta", [0.0, 0.005, 0.03, 0.0625, 0.07, 0.5, 0.99])
+def test_single_products(lib, n, k, q, delta):
+    _check_single_products(lib, n, k, q, delta)
+
+
+def test_single_products_signs_and_reproducible(lib):
+    _check_single_products(lib, 300, 16, 8, 0.03, signs=True)
+    _check_single_products(lib, 300, 16, 8, 0.03, deterministic=True)
