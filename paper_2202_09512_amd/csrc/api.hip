@@ -168,18 +168,18 @@ hipError_t dense_pass(nnrescal_handle* h, int only_slice, bool pq_cleared) {
       h->aop_valid = true;
     }
   }
-  const DensePlan pl = dense_stream_plan(d);
+  const DensePlan pl = dense_stream_plan(d, h->p.delta != 0.0f, h->det_ppart != nullptr);
   so.Ppart = h->det_ppart;                         // reproducible mode: panel sums stored, added up in order below
   so.timeout_flag = h->dev_error;
   so.spin_limit = h->p.handover_spin_limit;
   if (pl.full_members > 0) {
     Prof pf(h, 1);
-    if ((e = launch_dense_stream(X, h->A_op, P, Q, d, 0, h->p.seed, h->p.delta, h->stream, so)) != hipSuccess)
+    if ((e = launch_dense_stream(X, h->A_op, P, Q, d, pl, 0, h->p.seed, h->p.delta, h->stream, so)) != hipSuccess)
       return e;
   }
   if (pl.tail_members > 0) {
     Prof pf(h, 4);
-    e = launch_dense_stream(X, h->A_op, P, Q, d, 1, h->p.seed, h->p.delta, h->stream, so);
+    e = launch_dense_stream(X, h->A_op, P, Q, d, pl, 1, h->p.seed, h->p.delta, h->stream, so);
   }
   if (e == hipSuccess && h->det_ppart) {
     Prof pf(h, 3);

@@ -115,13 +115,20 @@ hipError_t launch_pack_operand(const float* A_int, float* A_op, const Dims& d, h
 // For every slice t and member r: P[t][i][r][:] = sum_j X[t][i][j] Delta^r[t][i][j] A[j][r][:],
 //                                 Q[t][j][r][:] = sum_i X[t][i][j] Delta^r[t][i][j] A[i][r][:].
 // P and Q must be zero on entry (partial sums are added atomically); the launcher does not clear them.
-// The members are taken in groups, each group's elements drawn from one Philox block.  part 0 = the members of whole groups
-// of 8 (4 for kp = 32, 2 above; on small tensors all members, in one launch), part 1 = the others; a part with no members
-// launches nothing.
+// The members are taken in groups, each group's elements drawn from one Philox block.  part 0 = all members, or those of
+// whole groups of 8 (4 for kp = 32, 2 above); part 1 = the others, or all of an ensemble smaller than such a group; a part with
+// no members launches nothing.
+struct StreamPart {
+  int waves, members, groups;    // per workgroup; per group; groups in the launch (0: no launch)
+  int64_t chunks;                // of rows
+  double us;                     // the estimate that it was chosen by
+};
 struct DensePlan {
   int full_members, tail_members;
+  StreamPart part[2];
 };
-DensePlan dense_stream_plan(const Dims& d);
+// perturb: delta > 0; ordered: for the reproducible mode (DenseStreamOpts::Ppart given)
+DensePlan dense_stream_plan(const Dims& d, bool perturb, bool ordered);
 int64_t dense_stream_panels(const Dims& d);   // 128-column panels of a slice
 struct DenseStreamOpts {
   int t_first = 0;               // slice index that X (and P, Q) start at, for callers that pass a part of the tensor:
@@ -139,8 +146,8 @@ struct DenseStreamOpts {
   int spin_limit = 0;            // polls a wave makes while it waits for its neighbour (0: the default, 2^20;
                                  // negative: none, every wait runs out at once)
 };
-hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int part,
-                               uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o = DenseStreamOpts());
+hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, float* Q, const Dims& d, const DensePlan& plan,
+                               int part, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o = DenseStreamOpts());
 hipError_t launch_dense_perturb(const float* X, float* out, int64_t n, int m, int member, uint64_t seed,
                                 float delta, hipStream_t s);
 // xn[r] += sum (X * Delta^r)^2 over all slices (double [q], zeroed by the caller)

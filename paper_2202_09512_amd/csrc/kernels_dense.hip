@@ -475,7 +475,8 @@ const char* dense_stream_kernel_name() { return "dense_stream_kernel"; }
 
 template <int NT, int QB, bool PERTURB, int W>
 static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qfirst,
-                                  int ngroups, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+                                  const StreamPart& part, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  const int ngroups = part.groups;
   const int t_first = o.t_first;
   const float* A_opQ = o.A_opQ ? o.A_opQ : A_op;
   const int64_t out_tstride = o.out_tstride < 0 ? d.n * d.q * (int64_t)d.kp : o.out_tstride;
@@ -494,27 +495,10 @@ static hipError_t launch_stream_t(const float* X, const float* A_op, float* P, f
     if (e != hipSuccess) return e;
     attr_done = true;
   }
+  // (a whole number of rounds of W strips; reproducible mode: one workgroup per panel and slice, the only writer of its X_t^T A)
   const int64_t n_panels = ceil_div(d.n, 16 * W);
-  // Rows are cut into chunks (whole rounds of 8 strips = 128 rows) so that the 256 CUs, one workgroup each at a
-  // time, are busy: more chunks even out the last wave of workgroups, fewer chunks save the fixed cost of a
-  // workgroup (clearing and adding out its share of Q, filling its pipeline: about 7 steps, i.e. the time of
-  // ~112 rows, measured).  Pick the count with the least estimated time.
-  const int64_t base = n_panels * d.m * ngroups;
-  const int64_t max_chunks = ceil_div(d.n, 16 * W);
-  int64_t n_chunks = 1, best = -1;
-  for (int64_t c = 1; c <= max_chunks && c <= 256; ++c) {
-    const int64_t rows = round_up(ceil_div(d.n, c), 16 * W);
-    const int64_t waves_of_wgs = ceil_div(base * ceil_div(d.n, rows), 256);
-    // (a single wave of workgroups measured 20 % slower than two of half the length: nothing overlaps its ends)
-    const int64_t cost = waves_of_wgs * (rows + 112) * (waves_of_wgs == 1 ? 5 : 4);
-    if (best < 0 || cost < best) {
-      best = cost;
-      n_chunks = c;
-    }
-  }
-  if (Ppart) n_chunks = 1;                          // one workgroup per panel and slice: the only writer of its X_t^T A
-  const int64_t rows_per_chunk = round_up(ceil_div(d.n, n_chunks), 16 * W);
-  n_chunks = ceil_div(d.n, rows_per_chunk);
+  const int64_t rows_per_chunk = round_up(ceil_div(d.n, Ppart ? 1 : part.chunks), 16 * W);
+  const int64_t n_chunks = ceil_div(d.n, rows_per_chunk);
   const int64_t total = n_panels * n_chunks * d.m * ngroups;
   if (total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL((dense_stream_kernel<NT, QB, PERTURB, W>), dim3((unsigned)total), dim3(W * 64), lds, s, X,
@@ -530,88 +514,108 @@ static int group_members(int kp) { return kp <= 16 ? 8 : (kp <= 32 ? 4 : 2); }
 
 int64_t dense_stream_panels(const Dims& d) { return ceil_div(d.n, kPanel); }
 
-// How a pass is cut into workgroups.  The big groups share the generator among the most members; a tensor whose blocks of
-// 128 x 128 elements, times groups, do not fill the 256 compute units has its time decided by the length of one
-// workgroup's chain of steps instead: it takes smaller groups (all members, a last group with empty slots included, in
-// one launch) and at last workgroups of 4 waves on blocks of 64 x 64.  Per pass, n / slices / members at rank <= 16,
-// big groups and tail -> the form taken here (us):
-//   4 waves, groups of 1:  100 / 2 / 4   21.7 -> 10.4     (of 2: 11.7)
-//   4 waves, groups of 2:  250 / 3 / 10  50.4 -> 13.4     (of 1: 15.4; 8 waves 18.2)
-//   8 waves, groups of 2:  333 / 5 / 10  49.6 -> 18.6     500 / 6 / 10  52.0 -> 29.5    (4 waves 20.6 and 33; of 4: 23.4 and 36.5)
-//   8 waves, groups of 4:  512 / 8 / 16  52.4 -> 46.4     (of 2: 48.5); with a tail, whose launch is saved,
-//                          1024 / 10 / 10  132 -> 125     2048 / 4 / 10  195 -> 185
-// and beyond: 1501 / 4 / 8 big groups 89, groups of 4 98; 2048 / 8 / 10 309 and 351.  (Rank 24 alike, with half the members
-// per group: 333 / 5 / 10 53.6 -> 26, 1024 / 4 / 10 106 -> 99.)
-struct StreamForm {
-  int waves, members;
-  bool merged;                                      // all members in one launch
-};
-static StreamForm stream_form(const Dims& d) {
-  const int big = group_members(d.kp), nt = d.kp / 16;
-  const auto blocks = [&](int side, int members) { return ceil_div(d.n, side) * ceil_div(d.n, side) * d.m * ceil_div(d.q, members); };
-  const int two = nt == 1 ? 2 : 1, four = nt == 1 ? 4 : (nt == 2 ? 2 : 1);
-  if (blocks(64, 1) <= 256) return {4, 1, true};
-  if (blocks(64, two) <= 512) return {4, two, true};
-  if (blocks(kPanel, two) <= 512 && nt <= 2) return {kWaves, two, true};
-  const int64_t b = blocks(kPanel, big);
-  if ((b <= 256 && nt <= 2) || (b <= 2048 && d.q % big != 0)) return {kWaves, four, true};
-  return {kWaves, big, false};
+// How a pass is cut into workgroups.  A launch takes its members in groups (the members of a group share the generator) on
+// panels of 16 W columns and chunks of rows.  Large groups generate least; many, small and short workgroups fill the 256
+// compute units and even out the last ones; few chunks add to Q least, wide panels to P.  The plan is the one of the least
+//   us = (1.25 ceil(B / C) - 0.25 max(1, B / C)) (rows (38 + 9 g + 8.5 g nt) ns + 1.3 g nt) + 0.3 / 10^6 additions to P + 1.25 / 10^6
+//        to Q,
+// B workgroups, C = 256 of them at a time (512 with 4 waves, whose rows take 5 % longer), g members of nt = kp / 16 column
+// blocks each.  g nt <= 2 leaves room for a second workgroup on a compute unit: without one (B <= C) the rows take 20 % longer.
+// A second launch costs 20 us more.  Fitted to 18560 timed launches (n = 100 ... 8000, 1 ... 20 slices, 1 ... 20 members, ranks
+// 5 ... 64, delta = 0.03, every form with up to 10 chunk counts) so that what it picks is fast, not to match the times: it takes
+// 0.95 % longer than the best one in the mean, 3 % at the ninetieth percentile, 11 % at the ninety-ninth, 19 % at worst.  At
+// delta = 0, where there is no generator and X is split once, 10 + 2 g takes the place of 38 + 9 g (4600 launches up to n = 4100:
+// 2 %, 8 %, 15 %, 20 %).
+// n / slices / members, rank: fp32 MFMA, the rule of size classes that stood here before, this plan (us for a pass):
+//   2000 / 4 / 1, 16    44.1   69.3   42.3        1000 / 4 / 7, 24    102    77.7   73.3
+//   2000 / 4 / 2, 16    55.8   80.4   57.7        1000 / 4 / 13, 64   268    223    177
+//   2000 / 4 / 5, 16    136    130    114         2000 / 4 / 15, 24   496    439    354
+//   2000 / 4 / 13, 16   298    245    207         2000 / 4 / 5, 64    335    283    258
+// Over 1051 sizes (15 shapes up to n = 8000, ranks 5 ... 64, 1 ... 20 members) this plan takes 0.95 of that rule's time in the mean,
+// 1.09 at worst, and 1.03 of fp32 MFMA's at worst (that rule: 1.57, with one or two members in groups of 4).
+static StreamPart stream_part(const Dims& d, int count, int waves, int members, bool perturb, bool ordered) {
+  StreamPart best{waves, members, (int)ceil_div(count, members), 1, 0.0};
+  const int nt = d.kp / 16, side = 16 * waves, width = members * nt;
+  const int64_t panels = ceil_div(d.n, side), most = ordered ? 1 : (panels < 256 ? panels : 256);
+  const double row_us = ((perturb ? 38.0 + 9.0 * members : 10.0 + 2.0 * members) + 8.5 * width) * (waves == 4 ? 1.05e-3 : 1e-3);
+  const double results = (double)d.m * d.n * count * d.k * 1e-6;   // values of P, and of Q, in millions
+  int64_t seen = 0;
+  for (int64_t c = 1; c <= most; ++c) {
+    const int64_t rows = round_up(ceil_div(d.n, c), side), chunks = ceil_div(d.n, rows);
+    if (chunks == seen) continue;                   // (the same cut again)
+    seen = chunks;
+    const int64_t blocks = panels * d.m * best.groups * chunks, at_once = waves == 4 ? 512 : 256;
+    const double rounds = 1.25 * ceil_div(blocks, at_once) - 0.25 * (blocks > at_once ? (double)blocks / at_once : 1.0);
+    const double alone = blocks <= at_once && width <= 2 ? 1.2 : 1.0;
+    const double us = rounds * ((rows < d.n ? rows : d.n) * row_us * alone + 1.3 * width) +
+                      (ordered ? 0.0 : results * (0.3 * panels + 1.25 * chunks));
+    if (c == 1 || us < best.us) {
+      best.chunks = chunks;
+      best.us = us;
+    }
+  }
+  return best;
 }
 
-DensePlan dense_stream_plan(const Dims& d) {
-  const int big = group_members(d.kp);
-  if (d.q >= big && stream_form(d).merged) return DensePlan{d.q, 0};
-  return DensePlan{d.q / big * big, d.q % big};
+// ordered: the reproducible mode (8 waves, one chunk: its copies of P are one per 128 columns, nothing is added)
+DensePlan dense_stream_plan(const Dims& d, bool perturb, bool ordered) {
+  const int big = group_members(d.kp), nt = d.kp / 16, tail = d.q % big;
+  DensePlan best{};
+  double best_us = -1.0;
+  for (int waves = ordered ? kWaves : 4; waves <= kWaves; waves *= 2)
+    for (int g = 1; g <= big && g < 2 * d.q; g *= 2) {
+      if (waves == 4 && g * nt > (nt > 2 ? nt : 2)) continue;   // (kernels that are not built)
+      const StreamPart p = stream_part(d, d.q, waves, g, perturb, ordered);
+      if (best_us < 0.0 || p.us < best_us) {
+        best_us = p.us;
+        best = d.q >= big ? DensePlan{d.q, 0, {p, {}}} : DensePlan{0, d.q, {{}, p}};
+      }
+    }
+  if (d.q > big && tail) {                          // the whole groups, and the rest in a group of its own
+    int g = 1;
+    while (g < tail) g *= 2;
+    const StreamPart whole = stream_part(d, d.q - tail, kWaves, big, perturb, ordered);
+    const StreamPart rest = stream_part(d, tail, kWaves, g, perturb, ordered);
+    if (whole.us + rest.us + 20.0 < best_us) best = DensePlan{d.q - tail, tail, {whole, rest}};
+  }
+  return best;
 }
 
 template <int NT, int QB, int W>
-static hipError_t launch_stream_qb(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int ngroups,
-                                   uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  if constexpr (QB * NT <= 8 && (W == kWaves || QB * NT <= (NT > 2 ? NT : 2))) {
-    return delta == 0.0f ? launch_stream_t<NT, QB, false, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o)
-                         : launch_stream_t<NT, QB, true, W>(X, A_op, P, Q, d, qf, ngroups, seed, delta, s, o);
-  }
+static hipError_t launch_stream_qb(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf,
+                                   const StreamPart& part, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  if constexpr (QB * NT <= 8 && (W == kWaves || QB * NT <= (NT > 2 ? NT : 2)))
+    return delta == 0.0f ? launch_stream_t<NT, QB, false, W>(X, A_op, P, Q, d, qf, part, seed, delta, s, o)
+                         : launch_stream_t<NT, QB, true, W>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
   return hipErrorInvalidValue;
 }
 
-// Members [qf, qf + count): whole groups in one launch, a rest in one of a group rounded up to a power of two; merged: all in
-// one launch.
 template <int NT>
-static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf, int count,
-                                   uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  const StreamForm f = stream_form(d);
-  int qb = f.members;
-  if (f.merged) count = (int)round_up(count, qb);
-  if (f.waves == 4 && !o.Ppart) {                   // (the reproducible mode's copies of P are one per 128 columns)
-    return qb == 1 ? launch_stream_qb<NT, 1, 4>(X, A_op, P, Q, d, qf, count, seed, delta, s, o)
-                   : launch_stream_qb<NT, 2, 4>(X, A_op, P, Q, d, qf, count / 2, seed, delta, s, o);
+static hipError_t launch_stream_nt(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int qf,
+                                   const StreamPart& part, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  if (part.waves == 4)
+    return part.members == 1 ? launch_stream_qb<NT, 1, 4>(X, A_op, P, Q, d, qf, part, seed, delta, s, o)
+                             : launch_stream_qb<NT, 2, 4>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
+  switch (part.members) {
+    case 1: return launch_stream_qb<NT, 1, kWaves>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
+    case 2: return launch_stream_qb<NT, 2, kWaves>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
+    case 4: return launch_stream_qb<NT, 4, kWaves>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
+    case 8: return launch_stream_qb<NT, 8, kWaves>(X, A_op, P, Q, d, qf, part, seed, delta, s, o);
+    default: return hipErrorInvalidValue;
   }
-  hipError_t e = hipSuccess;
-  while (count > 0 && e == hipSuccess) {
-    while (qb / 2 >= count) qb /= 2;
-    const int groups = count < qb ? 1 : count / qb;
-    switch (qb) {
-      case 1: e = launch_stream_qb<NT, 1, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      case 2: e = launch_stream_qb<NT, 2, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      case 4: e = launch_stream_qb<NT, 4, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-      default: e = launch_stream_qb<NT, 8, kWaves>(X, A_op, P, Q, d, qf, groups, seed, delta, s, o); break;
-    }
-    qf += groups * qb;
-    count -= groups * qb;
-  }
-  return e;
 }
 
-hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, float* Q, const Dims& d, int part,
-                               uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
-  const DensePlan pl = dense_stream_plan(d);
-  const int qf = part == 0 ? 0 : pl.full_members, count = part == 0 ? pl.full_members : pl.tail_members;
-  if (count == 0) return hipSuccess;
+hipError_t launch_dense_stream(const float* X, const float* A_op, float* P, float* Q, const Dims& d, const DensePlan& plan,
+                               int part, uint64_t seed, float delta, hipStream_t s, const DenseStreamOpts& o) {
+  const int qf = part == 0 ? 0 : plan.full_members;
+  const StreamPart& sp = plan.part[part];
+  if (sp.groups == 0) return hipSuccess;
+  if (o.Ppart && sp.waves != kWaves) return hipErrorInvalidValue;   // (a plan for the other mode)
   switch (d.kp / 16) {
-    case 1: return launch_stream_nt<1>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
-    case 2: return launch_stream_nt<2>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
-    case 3: return launch_stream_nt<3>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
-    case 4: return launch_stream_nt<4>(X, A_op, P, Q, d, qf, count, seed, delta, s, o);
+    case 1: return launch_stream_nt<1>(X, A_op, P, Q, d, qf, sp, seed, delta, s, o);
+    case 2: return launch_stream_nt<2>(X, A_op, P, Q, d, qf, sp, seed, delta, s, o);
+    case 3: return launch_stream_nt<3>(X, A_op, P, Q, d, qf, sp, seed, delta, s, o);
+    case 4: return launch_stream_nt<4>(X, A_op, P, Q, d, qf, sp, seed, delta, s, o);
     default: return hipErrorInvalidValue;
   }
 }

@@ -335,8 +335,9 @@ nnrescal_status start_nndsvd_impl(nnrescal_handle* h, int svd_iters, int r_iters
         so.out_tstride = 0;
         so.timeout_flag = h->dev_error;
         so.spin_limit = h->p.handover_spin_limit;
-        HIPCHK(launch_dense_stream(h->X.dense, opQ, Y, Y, d, 0, h->p.seed, h->p.delta, s, so));
-        HIPCHK(launch_dense_stream(h->X.dense, opQ, Y, Y, d, 1, h->p.seed, h->p.delta, s, so));
+        const DensePlan pl = dense_stream_plan(d, h->p.delta != 0.0f, false);
+        HIPCHK(launch_dense_stream(h->X.dense, opQ, Y, Y, d, pl, 0, h->p.seed, h->p.delta, s, so));
+        HIPCHK(launch_dense_stream(h->X.dense, opQ, Y, Y, d, pl, 1, h->p.seed, h->p.delta, s, so));
       }
       // ---- Y <- Y V L^-1 (columns of about unit length), then Cholesky QR into A
       for (int r = 0; r < q; ++r)

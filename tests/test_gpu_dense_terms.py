@@ -61,8 +61,7 @@ def test_products_range_and_signs(lib, xscale):
     _check(lib, 200, 1, 20, 3, 0.03, xscale=xscale, signs=True)
 
 
-# one size for each way a pass is cut into workgroups: 4 waves with groups of 1 and of 2 members, 8 waves with groups of 2 and
-# of 4 (a last group with empty slots among them) and with the largest groups, without and with a tail
+# larger ensembles, several slices (a call of nnrescal_products is a launch for ONE slice)
 @pytest.mark.parametrize("n,m,k,q", [(100, 2, 8, 4), (250, 3, 10, 9), (333, 5, 8, 9), (333, 5, 24, 9), (500, 8, 3, 15),
                                      (600, 4, 24, 9), (600, 4, 40, 5), (600, 7, 16, 16), (1501, 8, 3, 9)])
 @pytest.mark.parametrize("delta", [0.0, 0.03, 0.5])
@@ -96,13 +95,57 @@ def _check_single_products(lib, n, k, q, delta, deterministic=False, signs=False
         assert worst <= 1.5 * 2.0 ** -22 and (rms <= 2.0 ** -24.5 or n * q * k < 1000), (n, k, q, delta, "PQ"[which], worst, rms)
 
 
-@pytest.mark.parametrize("n,k,q", [(17, 3, 1), (130, 8, 4), (333, 8, 10), (1000, 16, 15), (2176, 16, 8), (2176, 32, 4), (640, 64, 3),
-                                   (4200, 16, 13)])
-@pytest.mark.parametrize("delta", [0.0, 0.005, 0.03, 0.0625, 0.07, 0.5, 0.99])
+# (n, k, q) of one slice: every kernel that the plan of a pass can choose (test_dense_plan.py holds the list to that)
+FORMS = [(17, 3, 1), (333, 8, 10), (700, 16, 8), (2001, 16, 1), (2001, 16, 2), (1000, 16, 15), (2176, 16, 8), (4200, 16, 13), (6001, 16, 9),
+         (6000, 16, 10), (6001, 16, 11), (33, 17, 2), (1001, 24, 2), (1001, 24, 7), (2502, 32, 4), (6001, 24, 5), (6000, 24, 6),
+         (300, 40, 5), (2001, 40, 2), (3000, 40, 3), (6001, 40, 5), (640, 64, 3), (2001, 64, 1), (2500, 64, 2), (6001, 64, 3), (2001, 40, 6),
+         (3000, 64, 4)]
+
+
+@pytest.mark.parametrize("n,k,q", FORMS)
+@pytest.mark.parametrize("delta", [0.0, 0.03, 0.5])
 def test_single_products(lib, n, k, q, delta):
+    _check_single_products(lib, n, k, q, delta)
+
+
+@pytest.mark.parametrize("n,k,q", [(130, 8, 4), (2176, 16, 8)])
+@pytest.mark.parametrize("delta", [1e-6, 0.005, 0.0624, 0.0625, 0.07, 0.99])
+def test_single_products_for_any_delta(lib, n, k, q, delta):
     _check_single_products(lib, n, k, q, delta)
 
 
 def test_single_products_signs_and_reproducible(lib):
     _check_single_products(lib, 300, 16, 8, 0.03, signs=True)
     _check_single_products(lib, 300, 16, 8, 0.03, deterministic=True)
+
+
+@pytest.mark.parametrize("n,m,k,q", [(90, 6, 5, 3), (600, 5, 16, 13), (600, 5, 24, 6), (500, 3, 40, 3), (300, 7, 64, 2), (1500, 4, 16, 8)])
+@pytest.mark.parametrize("delta", [0.0, 0.03])
+def test_single_products_in_one_launch_for_all_slices(lib, n, m, k, q, delta):
+    """An iteration's launch covers all slices.  X_t with one entry per row and column and R_t = 0 but for one slice s, where it is
+    diagonal (zeros stay), leave (P_s + Q_s)[i][c], two products, in the new A[i][c] = A R_s (P_s + Q_s) / (A W).  Against one
+    iteration in 64 bits, element by element: 2^-21.4 of the products, and a few 2^-23 each of R (a quotient of sums), W and
+    the quotient: 2^-20.  A lost term is 2^-17 or more."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + m)
+    rows = torch.arange(n, device=DEV)
+    X = torch.zeros((m, n, n), device=DEV)
+    for t in range(m):
+        X[t, rows, torch.randperm(n, generator=g, device=DEV)] = 1.0 + torch.rand(n, generator=g, device=DEV)
+    A = 1.0 + torch.rand((q, n, k), generator=g, device=DEV)
+    Xq = [(lib.nnrescal_perturb(lib.DenseX(X), r, delta, 7) if delta > 0 else X) for r in range(q)]
+    for s in range(m):
+        R = torch.zeros((q, m, k, k), device=DEV)
+        R[:, s] = torch.eye(k, device=DEV)
+        h = lib.nnrescal_init(lib.DenseX(X), k=k, q=q, delta=delta, seed=7, A0=A, R0=R, fused_small=False)
+        lib.nnrescal_mu_step(h)
+        got, _ = lib.nnrescal_get_factors(h)
+        lib.nnrescal_destroy(h)
+        for r in range(q):
+            x, a, rt = Xq[r][s].double(), A[r].double(), R[r, s].double()
+            gram = a.T @ a
+            rt = rt * (a.T @ (x @ a)) / (gram @ rt @ gram)
+            num = (x @ a) @ rt.T + (x.T @ a) @ rt
+            want = a * num / (a @ (rt @ gram @ rt.T + rt.T @ gram @ rt))
+            err = ((got[r].double() - want) / want).abs().max().item()
+            assert err <= 2.0 ** -20, (n, m, k, q, delta, s, r, err)
