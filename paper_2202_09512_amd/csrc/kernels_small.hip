@@ -227,15 +227,19 @@ hipError_t launch_from_internal_single(float* A_api_nk, const float* M, int ldm,
 // ------------------------------------------------------------------------------------------ Gram
 // out[a][c] += sum over this block's rows of Y[i][a] * Z[i][c] (the "gram_mul" class of the paper's
 // timing breakdown: A^T A of Alg. 3's first statement, A^T (X_t A), and the similarity products of
-// Alg. 5 and Alg. 6).  A block owns a TW x TW output tile; its 256 threads form 256/(TW/4)^2 groups that
-// take interleaved rows, each thread a 4 x 4 register tile; partial tiles are added with atomics.
+// Alg. 5 and Alg. 6).  A block owns a TW x TW output tile; its 1024 threads form 1024/(TW/4)^2 groups that take
+// interleaved rows, each thread a 4 x 4 register tile; the groups' tiles are added up in LDS in a fixed order, and the
+// blocks' sums with atomics: a product over one block of rows has the same bits every time.
+constexpr int kGramThreads = 1024;
 template <int TW>
-__global__ void __launch_bounds__(256) gram_kernel(GramArgs g, int64_t rows_per_block, int nsplit) {
+__global__ void __launch_bounds__(kGramThreads) gram_kernel(GramArgs g, int64_t rows_per_block, int nsplit) {
   constexpr int RT = 64;                   // rows staged per step
+  constexpr int LD = TW + 4;
   constexpr int TG = (TW / 4) * (TW / 4);  // threads per group
-  constexpr int NG = 256 / TG;
-  __shared__ float Ys[RT][TW + 4];
-  __shared__ float Zs[RT][TW + 4];
+  constexpr int NG = kGramThreads / TG;
+  constexpr int kSums = kGramThreads / 2 * 16;                  // tiles of half of the groups
+  __shared__ float lds[2 * RT * LD > kSums ? 2 * RT * LD : kSums];
+  float *Ys = lds, *Zs = lds + RT * LD;
   const int batch = blockIdx.z / nsplit;
   const int split = blockIdx.z % nsplit;
   const int b1 = batch / g.nb2, b2 = batch % g.nb2;
@@ -250,20 +254,20 @@ __global__ void __launch_bounds__(256) gram_kernel(GramArgs g, int64_t rows_per_
   int64_t r_end = r_begin + rows_per_block;
   if (r_end > g.n) r_end = g.n;
   for (int64_t r0 = r_begin; r0 < r_end; r0 += RT) {
-    for (int idx = tid; idx < RT * TW; idx += 256) {
+    for (int idx = tid; idx < RT * TW; idx += kGramThreads) {
       const int rr = idx / TW, cc = idx % TW;
       const int64_t row = r0 + rr;
       const bool ok = row < r_end;
-      Ys[rr][cc] = (ok && a0 + cc < g.wa) ? Yb[row * g.ldy + a0 + cc] : 0.0f;
-      Zs[rr][cc] = (ok && c0 + cc < g.wb) ? Zb[row * g.ldz + c0 + cc] : 0.0f;
+      Ys[rr * LD + cc] = (ok && a0 + cc < g.wa) ? Yb[row * g.ldy + a0 + cc] : 0.0f;
+      Zs[rr * LD + cc] = (ok && c0 + cc < g.wb) ? Zb[row * g.ldz + c0 + cc] : 0.0f;
     }
     __syncthreads();
     for (int rr = grp; rr < RT; rr += NG) {
       float y[4], z[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        y[u] = Ys[rr][ta + u];
-        z[u] = Zs[rr][tb + u];
+        y[u] = Ys[rr * LD + ta + u];
+        z[u] = Zs[rr * LD + tb + u];
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -272,6 +276,20 @@ __global__ void __launch_bounds__(256) gram_kernel(GramArgs g, int64_t rows_per_
     }
     __syncthreads();
   }
+  // the upper half of the groups hands its tiles to the lower one until one group is left
+  for (int half = NG / 2; half > 0; half /= 2) {
+    if (grp >= half && grp < 2 * half) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) lds[e * (half * TG) + tid - half * TG] = acc[e / 4][e % 4];
+    }
+    __syncthreads();
+    if (grp < half) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e / 4][e % 4] += lds[e * (half * TG) + tid];
+    }
+    __syncthreads();
+  }
+  if (grp != 0) return;
   float* ob = g.out + batch * g.obatch;
 #pragma unroll
   for (int u = 0; u < 4; ++u)
@@ -291,21 +309,22 @@ hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
   const int w = g.wa > g.wb ? g.wa : g.wb;
   const int TW = w <= 16 ? 16 : (w <= 32 ? 32 : 64);
   const int tiles = (int)(ceil_div(g.wa, TW) * ceil_div(g.wb, TW));
-  // enough blocks to fill the chip, but at least 512 rows each to keep the atomic traffic small; where that leaves compute
-  // units idle a block's chain of 64-row steps (10 us each, loads not overlapped) is the time: one step per block then
-  // (the sweep of ranks 2 ... 6 on 500 entities, 6 slices, 8 members: 11.6 -> 10.8 ms)
+  // enough blocks to fill the chip, but at least 512 rows each to keep the atomic traffic small; more than 512 rows that leave
+  // compute units idle that way go in steps of 64 per block instead.  Up to 512 rows are one block, so that their sums have the
+  // same bits every time (the sweep of ranks 2 ... 6 on 500 entities, 6 slices, 8 members: 10.5 ms, with blocks of 64 rows 10.4,
+  // with one block of 256 threads 11.3)
   const int64_t want_split = ceil_div(2048, (int64_t)tiles * nbatch);
-  const int64_t least = (int64_t)tiles * nbatch * ceil_div(g.n, 512) < 256 ? 64 : 512;
+  const int64_t least = g.n > 512 && (int64_t)tiles * nbatch * ceil_div(g.n, 512) < 256 ? 64 : 512;
   int64_t rows_per_block = round_up(ceil_div(g.n, want_split), 64);
   if (rows_per_block < least) rows_per_block = least;
   const int nsplit = (int)ceil_div(g.n, rows_per_block);
   dim3 grid((unsigned)ceil_div(g.wa, TW), (unsigned)ceil_div(g.wb, TW), (unsigned)(nbatch * nsplit));
   if (TW == 16)
-    hipLaunchKernelGGL(gram_kernel<16>, grid, dim3(256), 0, s, g, rows_per_block, nsplit);
+    hipLaunchKernelGGL(gram_kernel<16>, grid, dim3(kGramThreads), 0, s, g, rows_per_block, nsplit);
   else if (TW == 32)
-    hipLaunchKernelGGL(gram_kernel<32>, grid, dim3(256), 0, s, g, rows_per_block, nsplit);
+    hipLaunchKernelGGL(gram_kernel<32>, grid, dim3(kGramThreads), 0, s, g, rows_per_block, nsplit);
   else
-    hipLaunchKernelGGL(gram_kernel<64>, grid, dim3(256), 0, s, g, rows_per_block, nsplit);
+    hipLaunchKernelGGL(gram_kernel<64>, grid, dim3(kGramThreads), 0, s, g, rows_per_block, nsplit);
   return hipGetLastError();
 }
 

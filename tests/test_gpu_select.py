@@ -65,6 +65,15 @@ def test_cluster_matches_oracle(lib, n, m, k, q):
     assert abs(got["s_min"] - s_min) < 2e-5 and abs(got["s_avg"] - s_avg) < 2e-5
 
 
+@pytest.mark.parametrize("n,k,q", [(65, 3, 4), (150, 2, 20), (300, 10, 4), (448, 5, 8), (512, 6, 8), (512, 20, 16)])
+def test_cluster_repeats_bit_for_bit_up_to_512_entities(lib, n, k, q):
+    """The similarity products of up to 512 entities are one workgroup's sums per tile, in a fixed order."""
+    A_ens, _, _ = _planted_ensemble(n, 1, k, q, 0.4, n + k)
+    A = torch.from_numpy(A_ens).to(DEV)
+    seen = {(got["s_min"], got["s_avg"], str(got["perm"])) for got in (lib.nnrescal_cluster(A, None) for _ in range(25))}
+    assert len(seen) == 1, seen
+
+
 def test_cluster_recovers_planted_permutations(lib):
     A_ens, R_ens, perms = _planted_ensemble(400, 2, 6, 7, 0.02, 3)
     got = lib.nnrescal_cluster(torch.from_numpy(A_ens).to(DEV), None)
