@@ -108,9 +108,7 @@ def shapes(rng, count, waves):
         yield n, rows, int(rng.integers(n_panels))
 
 
-@pytest.mark.parametrize("waves", [8, 4])
-@pytest.mark.parametrize("style", ["uniform", "bursts", "laggard"])
-def test_every_column_has_one_owner_at_any_time(style, waves):
+def _one_owner_at_any_time(style, waves):
     rng = np.random.default_rng({"uniform": 1, "bursts": 2, "laggard": 3}[style])
     # the shapes of the GPU regression test (ragged last rounds) and random ones
     fixed = [(685, 685, 5), (685, 344, 0), (300, 300, 2), (1000, 504, 7), (130, 130, 1), (17, 17, 0), (2048, 2048, 3)]
@@ -120,6 +118,16 @@ def test_every_column_has_one_owner_at_any_time(style, waves):
         # every (strip, tile) of the chunk went through its column phase exactly once, and every wave made every step
         assert len(wg.strip_tiles) == wg.nstrips * wg.tiles and wg.col_work.sum() == wg.nstrips * wg.tiles
         assert wg.done == [wg.nsteps] * waves and wg.owner == [None] * waves
+
+
+@pytest.mark.parametrize("style", ["uniform", "bursts", "laggard"])
+def test_every_column_has_one_owner_at_any_time(style):
+    _one_owner_at_any_time(style, 8)
+
+
+@pytest.mark.parametrize("style", ["uniform", "bursts", "laggard"])
+def test_every_column_has_one_owner_with_four_waves(style):
+    _one_owner_at_any_time(style, 4)
 
 
 def test_model_catches_idle_waves_that_do_not_wait():
