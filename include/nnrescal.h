@@ -62,7 +62,10 @@ enum { NNRESCAL_DENSE = 0, NNRESCAL_CSR = 1, NNRESCAL_CSR_CSC = 2 };
 
 /* The input tensor (n x n x m, non-negative).  All pointers are DEVICE pointers, borrowed.
  *   format NNRESCAL_DENSE:   dense[m][n][n], fp32, slice-major, each slice row-major (Alg. 1 states
- *                            X as m x n x n); the other pointers are ignored.
+ *                            X as m x n x n); the other pointers are ignored.  The products with the factors
+ *                            keep every fp32 operand as a sum of three bf16 terms, exactly from 2^-110 (7.7e-34) up;
+ *                            smaller entries of X or of a factor lose up to their last 16 bits.  A factor or an X
+ *                            with an infinity gives NaN in the rows and columns that it takes part in.
  *   format NNRESCAL_CSR:     per slice t a CSR matrix: csr_rowptr[t*(n+1) .. ] (n+1 int64 offsets that
  *                            are local to the slice), column indices and values of slice t start at
  *                            csr_slice_off[t] (HOST array of m+1 int64) inside csr_col / csr_val.
@@ -306,12 +309,12 @@ NNRESCAL_API const char *nnrescal_last_error(const nnrescal_handle *h_or_null);
  * NULL), then switches profiling on (enable != 0: counters are reset) or off; enable == 2 times only the
  * passes over X and the A rule (classes 1, 2, 4 and 5), which perturbs a timed run less.  Classes follow the
  * paper's timing breakdown (section "Scalability"): 0 gram_mul (A^T A, A^T (X_t A)), 1 matrix_mul: the
- * dense pass over X for the groups of 8 members (4 for ranks 17 ... 32, 2 above; on small tensors for all
- * members of an ensemble of at least that many; one event pair = one kernel launch over all slices),
+ * dense pass over X for an ensemble of at least 8 members (4 for ranks 17 ... 32, 2 above): all of them, or the multiple of
+ * that number where the rest has a launch of its own (one event pair = one kernel launch over all slices),
  * 2 matrix_mul_sparse (with a CSC copy one pair per iteration: the launch that clears shared rows and the launch of
  * both products of all slices; without one, a pair for X_t A of all slices and one per slice for the scatter form of
  * X_t^T A), 3 element-wise and k x k update kernels,
- * 4 the dense pass for the tail group of fewer than 8 members (one pair), 5 the A rule (the
+ * 4 the dense pass for that rest, or for an ensemble of fewer members than that (one pair), 5 the A rule (the
  * n x k x k products of Eq. 2's second rule and the update itself; one pair per iteration, including the A^T A
  * pass that follows it for ranks above 32). */
 #define NNRESCAL_PROF_CLASSES 6

@@ -11,14 +11,14 @@
 // operand, built in registers by the lane that loaded the element; rows of the factor are the right operand, read from
 // a copy of A that is stored in operand order (two 16-byte loads per lane and product group).
 //
-// A workgroup of W = 8 waves (4 on small tensors) owns a panel of 16 W columns (W tiles) and a chunk of rows.  In a round, every wave
-// takes one 16-row strip and walks it across the panel, tile by tile:
+// A workgroup of W = 8 or 4 waves owns a panel of 16 W columns (W tiles) and a chunk of rows.  In a round, every wave takes
+// one 16-row strip and walks it across the panel, tile by tile:
 //   - the strip's P accumulators and the right operands of the Q products (the strip's 16 factor rows) stay
 //     in registers for the whole strip; P is added to memory once per strip;
 //   - the tile's terms are parked in LDS and read back transposed (ds_read_b64_tr_b16) for the Q product, so the
 //     generator and the split into terms run once per element;
 //   - the panel's Q accumulators live in LDS in accumulator order.  In step s wave w works on tile
-//     (w + s) % 8, so at any time each tile column has one owner, which adds the tile's products to the
+//     (w + s) % W, so at any time each tile column has one owner, which adds the tile's products to the
 //     accumulators: no atomics and no cross-wave reduction.  (The bf16 instruction cuts what lies 2^-8 of its C
 //     operand's last place or deeper.  Over the thousands of instructions of a chunk that added up to 2.8e-7 of Q, always
 //     downwards; with a tile's products summed from zero and added by vector instructions Q is off by 1.5e-9 in the
@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(W * 64, 2)
   const uintx4* Ap = A_op + (int64_t)t * aop_tstride + (int64_t)q0 * NT * 128 +
                      (jp0 >> 4) * tile_u4;          // operands of the panel's column tiles, first group of this member group
 
-  // A round = 8 strips of 16 rows, one per wave; in step s of a round wave w works on tile (w + s) % 8 of
+  // A round = W strips of 16 rows, one per wave; in step s of a round wave w works on tile (w + s) % W of
   // its strip, so at any step every tile column of the Q accumulator belongs to one wave.  A column passes from
   // wave w + 1 to wave w; instead of a barrier per step each wave counts its completed steps in LDS and waits
   // only for the one wave it takes its column from.
@@ -367,11 +367,11 @@ __global__ void __launch_bounds__(W * 64, 2)
       bp_fetch(tile_of((s + 1) & (W - 1)));
       if (work) {
         // ---- "column" orientation read back from LDS: lane (l16, row) gets the terms of rows i0 + 4*row + r of column
-        //      j0 + l16; the tile's Q accumulators are this wave's alone until the next barrier
+        //      j0 + l16; the tile's Q accumulators are this wave's alone until its step count moves
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // Tile column jt was wave (wave + 1) % 8's in the previous step: wait until that wave has completed it.
+        // Tile column jt was wave (wave + 1) % W's in the previous step: wait until that wave has completed it.
         const bool mine = wait_for_neighbour(rnd * W + s);   // wave-uniform
         float4* qt = reinterpret_cast<float4*>(qlds) + (jt * NG) * 64 + lane;
         // QH members at a time: all LDS reads first (one wait), then the products back to back, then the stores (with all

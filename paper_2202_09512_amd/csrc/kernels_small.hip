@@ -311,8 +311,8 @@ hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
   const int tiles = (int)(ceil_div(g.wa, TW) * ceil_div(g.wb, TW));
   // enough blocks to fill the chip, but at least 512 rows each to keep the atomic traffic small; more than 512 rows that leave
   // compute units idle that way go in steps of 64 per block instead.  Up to 512 rows are one block, so that their sums have the
-  // same bits every time (the sweep of ranks 2 ... 6 on 500 entities, 6 slices, 8 members: 10.5 ms, with blocks of 64 rows 10.4,
-  // with one block of 256 threads 11.3)
+  // same bits every time (the sweep of ranks 2 ... 6 on 500 entities, 6 slices, 8 members: 10.5 ms; blocks of 64 rows 10.4, and
+  // 0.8 ms less than one block of 256 threads)
   const int64_t want_split = ceil_div(2048, (int64_t)tiles * nbatch);
   const int64_t least = g.n > 512 && (int64_t)tiles * nbatch * ceil_div(g.n, 512) < 256 ? 64 : 512;
   int64_t rows_per_block = round_up(ceil_div(g.n, want_split), 64);
