@@ -159,6 +159,9 @@ const char* dense_stream_kernel_name();
 
 // ---- tensors that fit one CU's LDS (kernels_tiny.hip): `iters` whole iterations in one launch, one workgroup per member
 bool tiny_fit_applies(const Dims& d);
+// columns read at once; row pitches of the n x k arrays and of the k x k matrices in LDS
+struct TinyPitch { int columns, kc, kr; };
+TinyPitch tiny_fit_pitch(const Dims& d);
 hipError_t launch_tiny_fit(const float* X, float* A_int, float* R, const Dims& d, int iters, float eps, uint64_t seed,
                            float delta, hipStream_t s);
 

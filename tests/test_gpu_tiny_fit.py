@@ -9,7 +9,9 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("n,m,k,q", [(1, 1, 1, 2), (2, 3, 2, 3), (5, 1, 4, 1), (17, 2, 5, 9), (63, 3, 3, 2), (64, 8, 1, 2),
-                                     (20, 80, 1, 2), (64, 1, 56, 1), (33, 4, 16, 3), (30, 5, 30, 2)])
+                                     (20, 80, 1, 2), (64, 1, 56, 1), (33, 4, 16, 3), (30, 5, 30, 2),
+                                     # rows spaced in LDS (16, 32), not spaced for want of room, one column at a time
+                                     (16, 2, 16, 2), (40, 4, 32, 2), (34, 5, 30, 2), (64, 7, 7, 2), (31, 15, 13, 2), (62, 8, 5, 2)])
 @pytest.mark.parametrize("delta", [0.0, 0.03])
 def test_single_launch_fit_against_general_kernels(lib, n, m, k, q, delta):
     g = torch.Generator(device=DEV)
