@@ -40,8 +40,8 @@ CSRC = os.path.join(ROOT, "paper_2202_09512_amd", "csrc")
 # to the kernel the figure reads null until the counters have been taken again.
 RECORDED_TRAFFIC = {
     # (workload, k, kernel class): (bytes per launch, source file, sha256[:12] of that file, profile)
-    ("c3", 16, "matrix_mul"): (79.17e9, "kernels_dense.hip", "235161672732", "profiles/dense_stream_c3_k16.txt"),
-    ("c2", 16, "matrix_mul"): (0.908e9, "kernels_dense.hip", "235161672732", "profiles/dense_stream_c2_k16.txt"),
+    ("c3", 16, "matrix_mul"): (79.17e9, "kernels_dense.hip", "d0d37e29d9b7", "profiles/dense_stream_c3_k16.txt"),
+    ("c2", 16, "matrix_mul"): (0.908e9, "kernels_dense.hip", "d0d37e29d9b7", "profiles/dense_stream_c2_k16.txt"),
     ("c4", 32, "matrix_mul_sparse"): (44.78e9, "kernels_sparse.hip", "4f614c1e6a17", "profiles/spmm_gather_c4_k32.txt"),
     ("c5", 64, "matrix_mul_sparse"): (146.56e9, "kernels_sparse.hip", "4f614c1e6a17", "profiles/sparse_iteration_c5_k64.txt"),
 }

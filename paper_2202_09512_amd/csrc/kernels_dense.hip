@@ -29,7 +29,7 @@
 // work is shared by up to 8 members.
 //
 // What bounds it: the vector instructions of a tile (generator, splitting, conversions), with two waves per SIMD at 256
-// registers each; the additions of P to memory cost another 17 % (measured by leaving them out).  Against the kernel with
+// registers each; the additions of P to memory cost another 16 % (measured by leaving them out).  Against the kernel with
 // fp32 MFMA, one launch for all slices, any delta > 0: n = 16384, 4 slices, 8 members, rank 16: 7.05 -> 6.40 ms; n = 2160,
 // 20 slices, 8 members, rank 24: 1342 -> 1127 us; n = 2048, 8 slices, 6 members, rank 64: 674 -> 511 us.
 // Measured and left out: a head x1 = that of X, common to the members, with each member's distance from it in two terms
@@ -44,7 +44,7 @@ namespace nnr {
 // Issue priority of a wave by the phase of its step (s_setprio; it only orders the waves of a SIMD, not streams):
 // lowest in the long vector-only generator phase, higher once the matrix products start, highest from the tile
 // transposition to the end of the step.  The wave that is nearer to handing its tile column on goes first; measured at
-// n = 16384 (4 slices, 8 members): equal priorities 2 % slower, the opposite order 3 %.
+// n = 16384 (4 slices, 8 members): equal priorities 4 % slower, the opposite order 3 %.
 constexpr int kPrioGenerator = 0, kPrioPProducts = 1, kPrioRest = 2;
 
 constexpr int kWaves = 8;
@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(W * 64, 2)
         const bool mine = wait_for_neighbour(rnd * W + s);   // wave-uniform
         float4* qt = reinterpret_cast<float4*>(qlds) + (jt * NG) * 64 + lane;
         // QH members at a time: all LDS reads first (one wait), then the products back to back, then the stores (with all
-        // 8 groups at a time, or half of them, the registers run out)
+        // 8 groups at a time the registers run out; halves spill 10 and are 3 % slower than quarters at n = 16384)
         constexpr int QH = NG < 8 || QB == 1 ? QB : (QB > 2 ? QB / 4 : 1);
 #pragma unroll
         for (int q1 = 0; q1 < QB; q1 += QH) {
